@@ -40,7 +40,7 @@ FLOP_PER_AMP_DENSE1 = 14
 METRIC = "state-vector HBM GB/s vs peak; adjoint grad evals/s vs parameter-shift"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "tile_pass_brick30_traffic.txt")
 QAOA_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "tile_pass_adjoint_qaoa24_traffic.txt")
-TRAFFIC_SOURCES = ["qsv_kernels.hip", "engine.cpp", "api.cpp"]
+TRAFFIC_SOURCES = ["tile_rb.h", "qsv_kernels.hip", "engine.cpp", "api.cpp"]
 
 
 def sources_digest():

@@ -1,16 +1,23 @@
 """Build the HIP engine (libqsv.so) in-tree for gfx950 with hipcc."""
 
+import concurrent.futures
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqsv.so")
 
-SOURCES = ["qsv_kernels.hip", "engine.cpp", "api.cpp", "batch.cpp", "mpnn.hip", "noalloc.hip"]
+# Each source with its own definitions; the register-blocked passes compile once per amplitude
+# type, direction and launch form, so that their instantiations build in parallel.
+SOURCES = [("tile_rb.hip", [f"-DQSV_RB_REAL={r}", f"-DQSV_RB_ADJ={a}", f"-DQSV_RB_MULTI={m}"])
+           for r in ("double", "float") for a in ("true", "false") for m in (0, 1)]
+SOURCES += [(s, []) for s in ("tile_lds.hip", "qsv_kernels.hip", "engine.cpp", "api.cpp", "batch.cpp", "mpnn.hip",
+                              "noalloc.hip")]
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # Keep branches on wave-uniform values (the op type of a fused pass) as plain scalar
     # branches: structurizing them makes old and new register blocks live at once, and the
@@ -29,11 +36,7 @@ def hipcc():
     return cand if os.path.exists(cand) else "hipcc"
 
 
-def build(verbose=False):
-    """Compile every source into paper_2406_17248_amd/libqsv.so (always rebuilds)."""
-    srcs = [os.path.join(CSRC, s) for s in SOURCES]
-    tmp = LIB + ".tmp"
-    cmd = [hipcc()] + HIPCC_FLAGS + ["-I", os.path.join(HERE, "..", "include")] + srcs + ["-o", tmp]
+def run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -42,6 +45,19 @@ def build(verbose=False):
         raise RuntimeError(f"hipcc failed ({res.returncode}):\n{err}")
     if verbose and err.strip():
         print(err, file=sys.stderr)
+
+
+def build(verbose=False):
+    """Compile every source and link paper_2406_17248_amd/libqsv.so (always rebuilds)."""
+    tmp = LIB + ".tmp"
+    inc = ["-I", os.path.join(HERE, "..", "include")]
+    jobs = min(8, int(os.environ.get("MAX_JOBS", os.cpu_count() or 1)))
+    with tempfile.TemporaryDirectory() as d, concurrent.futures.ThreadPoolExecutor(jobs) as pool:
+        objs = [os.path.join(d, f"{i}.o") for i in range(len(SOURCES))]
+        cmds = [[hipcc()] + HIPCC_FLAGS + defs + inc + ["-c", os.path.join(CSRC, s), "-o", o]
+                for (s, defs), o in zip(SOURCES, objs)]
+        list(pool.map(lambda c: run(c, verbose), cmds))
+        run([hipcc(), "--offload-arch=gfx950", "-fPIC", "-shared"] + objs + ["-o", tmp], verbose)
     os.replace(tmp, LIB)
     return LIB
 

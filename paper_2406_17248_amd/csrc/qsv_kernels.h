@@ -1,4 +1,4 @@
-// Host-side launchers of the HIP kernels (defined in qsv_kernels.hip).
+// Host-side launchers of the HIP kernels.
 #pragma once
 #include <hip/hip_runtime_api.h>
 #include <stdint.h>
