@@ -225,6 +225,7 @@ hipError_t launch_pass(const qsv_state* s, const DevPass& dp, PassArgs A, int ba
   A.win_n = dp.rb ? dp.win_n : 0;
   A.pass_pslots = adj ? dp.pslot_count : 0;
   const uint64_t tiles = 1ull << (s->n - dp.m);
+  set_table_parts(A, dp, tiles * (uint64_t)batch <= kWarmTiles);
   A.n_tiles = (int64_t)tiles;
   if (dp.rb) return launch_tile_pass_rb(s->dtype, adj, dp.rb, dp.maxm, A, tiles, batch, s->stream);
   return launch_tile_pass(s->dtype, adj, dp.maxm, A, tiles, batch, s->stream);

@@ -1148,6 +1148,9 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
     dp.maxm = maxm;
     dp.rb = rb ? reg_bits : 0;
     dp.op_first = (int32_t)plan.ops.size();
+    dp.ctab_lo = plan.ctab_size;
+    dp.diag_lo = (int32_t)plan.diag.size();
+    dp.edge_lo = (int32_t)plan.edges.size();
     dp.pslot_first = plan.n_pslots;
     PassEmitter em{plan, c, adjoint, opt, ps.tile_mask, {}, {}};
     {
@@ -1419,6 +1422,9 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
       plan.n_pslots += dp.pslot_count;
     }
     dp.op_count = (int32_t)plan.ops.size() - dp.op_first;
+    dp.ctab_n = plan.ctab_size - dp.ctab_lo;
+    dp.diag_n = (int32_t)plan.diag.size() - dp.diag_lo;
+    dp.edge_n = (int32_t)plan.edges.size() - dp.edge_lo;
     if (rb) {
       dp.dep_first = (int32_t)plan.deps.size();
       const std::vector<int>& Lr = lay[pi];

@@ -138,7 +138,21 @@ struct DevPass {
   int32_t  win_lo, win_n;  // register-blocked: ctab window of the pass's per-lane lookups
   int32_t  dep_first;      // register-blocked: first of the pass's kDepEntries Plan::deps entries
   int32_t  relayout;       // register-blocked: stores go to another layout (and buffer)
+  int32_t  ctab_lo, ctab_n, diag_lo, diag_n, edge_lo, edge_n;  // the pass's parts of the tables
 };
+
+// Launches of at most this many tiles read the pass's tables into L2 ahead of use (four
+// workgroups per CU: beyond that other workgroups hide, or have done, the first reads).
+constexpr uint64_t kWarmTiles = 1024;
+inline void set_table_parts(PassArgs& A, const DevPass& dp, int32_t warm) {
+  A.ctab_lo = dp.ctab_lo;
+  A.ctab_n = dp.ctab_n;
+  A.diag_lo = dp.diag_lo;
+  A.diag_n = dp.diag_n;
+  A.edge_lo = dp.edge_lo;
+  A.edge_n = dp.edge_n;
+  A.warm = warm;
+}
 
 // A fully planned execution (forward or adjoint reverse sweep) of one circuit structure.
 // A fused block of primitives applied as one dense 8x8 matrix: q[b] is the global qubit of

@@ -158,6 +158,10 @@ struct PassArgs {
   int64_t      win_lo;
   int32_t      pass_pslots;   // adjoint: gradient slots (pslot values) used by this pass
   int32_t      relayout;      // 1: stores use their own tables and base (see kDepEntries)
+  // what the pass reads of the tables: ctab entries [ctab_lo, ctab_lo + ctab_n), diag entries
+  // [diag_lo, diag_lo + diag_n) and edges [edge_lo, edge_lo + edge_n)
+  int32_t      ctab_lo, ctab_n, diag_lo, diag_n, edge_lo, edge_n;
+  int32_t      warm;          // 1: read these ahead of their use
 };
 
 // Adjoint register-blocked passes keep each gradient slot's per-wave sums in LDS until the
