@@ -850,6 +850,27 @@ struct PassEmitter {
         continue;
       }
       close_block();
+      if (reg_index && p.type == P_DENSE1 && p.recipe == M_GATE && c->gates[p.gate].kind == QSV_GATE_X) {
+        if (pending_touched & p.nondiag) flush();
+        TileOp op{};
+        op.type = OP_FLIP;
+        op.a = reg_index[loc[p.q0]];
+        if (op.a < 0) fail(QSV_EINVAL, "internal: dense target is not a register bit");
+        op.gen = -1;
+        op.pslot = -1;
+        op.lmask = local_mask(p.cmask & T);
+        op.omask = p.cmask & ~T;
+        DiagEntry d{};  // the controls' thread part, and the slots that satisfy their slot part
+        d.lcmask = op.lmask;
+        slot_masks(d);
+        uint32_t pairs = 0;
+        for (int k = 0; k < (1 << lay.r); ++k)
+          if (!(k >> op.a & 1)) pairs |= d.kmask & (1u << k);
+        op.first = (int32_t)d.tmask;
+        op.plain = kPlainFlip | (1 + op.a) | (op.omask ? kPlainOutside : 0) | (int32_t)(pairs << 16);
+        push(op, -1);
+        continue;
+      }
       TileOp pre{};
       bool has_pre = false;
       if (pending_touched & p.nondiag) {

@@ -31,6 +31,11 @@ enum OpType : int32_t {
                   // slot bit `a` (bit 2), applied with matrix-core instructions (16x16x4):
                   // ctab[mat .. mat + 128) holds its real 16x16 form as each lane's four
                   // A-operand values, lane-major (see block_operands)
+  OP_FLIP = 7,    // register-blocked passes: X on register slot bit `a`, with or without
+                  // controls: amplitudes of a slot pair trade places.  plain = kPlainFlip |
+                  // (1 + a) | pairs << 16 (bit k of pairs: slot k, with the slot bit 0, and its
+                  // partner satisfy the controls on slots) (| kPlainOutside: omask is not 0);
+                  // first = the controls on thread bits, in j-space
 };
 // In register-blocked passes each thread holds 2^RB amplitudes; DENSE1 then names a
 // register-bit index (a in [0, RB)) instead of a local bit, and the other ops are
@@ -71,6 +76,7 @@ struct TileOp {
 };
 constexpr int32_t kPlainSigns = 8, kPlainBlock = 16;
 constexpr int32_t kPlainSplit = 32, kPlainReal = 64, kPlainXlike = 96, kPlainForm = 96;
+constexpr int32_t kPlainFlip = 128, kPlainOutside = 256;
 static_assert(offsetof(TileOp, plain) == 0 && offsetof(TileOp, gkind) == 28 && alignof(TileOp) == 8,
               "plain .. gkind form the record's first 32 bytes");
 // Generator forms of DENSE1 ops (k = the chain-rule factor, read from the generator table):
