@@ -730,6 +730,21 @@ struct PassEmitter {
       if ((bits & rm) == rm) d.kmask |= 1u << k;
     }
   }
+  // Where a diagonal entry's index bits come from in the current register layout.
+  void bit_sources(DiagEntry& d) const {
+    d.tab = d.mat;
+    d.gtab = d.gen;
+    d.where = (d.kind == DIAG_SIGN ? kWhereSign : 0) | (d.q1 >= 0 ? kWhereTwo : 0);
+    for (int b = 0; b < 2; ++b) {
+      const int q = b ? d.q1 : d.q0, l = b ? d.l1 : d.l0;
+      const int slot = (rb && l >= 0) ? lay.slot_of(l) : -1;
+      uint32_t bits = 0;
+      if (slot >= 0)
+        for (int k = 0; k < (1 << lay.r); ++k) bits |= (uint32_t)((k >> slot) & 1) << k;
+      (b ? d.bits1 : d.bits0) = bits;
+      d.where |= (q < 0 || slot >= 0 ? kNoBit : l >= 0 ? (uint32_t)l : 32u + (uint32_t)q) << (8 * b);
+    }
+  }
   // A ZZ edge with its thread-bit mask, outside-bit mask and (in pad, until the run is
   // sorted) its register class for the current register layout.
   ZZEdge edge_in_layout(int u, int v) const {
@@ -1021,6 +1036,7 @@ struct PassEmitter {
           d.gen = alloc(prim_size(q));
           plan.fills.push_back({F_PRIM_GEN, seq[e], 0, d.gen});
         }
+        bit_sources(d);
         plan.diag.push_back(d);
         ++e;
       }
@@ -1500,7 +1516,7 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
       plan.deps.resize(dp.dep_first + kDepEntries, 0);
     }
     if (rb) {
-      // ctab window of the per-lane lookups (ZZ phase / generator tables, phase entries)
+      // ctab window of the per-lane lookups (ZZ phase / generator tables)
       int64_t lo = INT64_MAX, hi = INT64_MIN;
       auto cover = [&](int64_t off, int64_t n) {
         if (off < 0) return;
@@ -1512,14 +1528,6 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
         if (o.type == OP_ZZ) {
           cover(o.mat, o.count + 1);
           cover(o.gen, o.count + 1);
-        } else if (o.type == OP_DIAG && o.b) {
-          for (int e = 0; e < o.count; ++e) {
-            const DiagEntry& d = plan.diag[o.first + e];
-            if (d.kind != DIAG_PHASE) continue;
-            const int n = d.q1 >= 0 ? 4 : 2;
-            cover(d.mat, n);
-            cover(d.gen, n);
-          }
         }
       }
       if (hi > lo && hi - lo <= kMaxWindow) {

@@ -107,7 +107,15 @@ struct DiagEntry {
   // register slot k has every register bit of lcmask set.  The local condition
   // (j & lcmask) == lcmask then reads ((j_thread & tmask) == tmask) && (kmask >> k & 1).
   uint32_t tmask, kmask;
+  // What a register-blocked pass reads of the entry follows ocmask in one piece: the table
+  // offsets again, and where the bits of q0 and q1 come from: bits0 / bits1 hold the slots
+  // whose bit is 1 when the qubit is on a slot bit (else 0), byte 0 / 1 of `where` the
+  // thread bit's local position, 32 + the global position of an outside bit, or kNoBit
+  // (slot bit, or no such qubit); bit 16 of `where`: SIGN entry, bit 17: two-qubit table.
+  int32_t  tab, gtab;
+  uint32_t where, bits0, bits1, pad;
 };
+constexpr uint32_t kNoBit = 255, kWhereSign = 1u << 16, kWhereTwo = 1u << 17;
 
 // One edge of an OP_ZZ run: global qubits (u, v) and their local bits in the pass's tile
 // (lu, lv; -1 when outside the tile).  For register-blocked passes, in the register layout

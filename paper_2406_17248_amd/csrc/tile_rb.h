@@ -383,6 +383,14 @@ static_assert(offsetof(DiagEntry, tmask) == offsetof(DiagEntry, ocmask) + 8 &&
 __device__ __forceinline__ SignFields sign_fields(const DiagEntry* d) {
   return ld_record(reinterpret_cast<const SignFields*>(&d->ocmask));
 }
+struct PhaseFields {
+  uint64_t ocmask;
+  uint32_t tmask, kmask;
+  int32_t tab, gtab;
+  uint32_t where, bits0, bits1, pad;
+};
+static_assert(offsetof(DiagEntry, pad) == offsetof(DiagEntry, ocmask) + offsetof(PhaseFields, pad),
+              "an entry's register-pass fields are contiguous");
 // Also returns in `touched` (wave-uniform) the slots any entry of the run can flip.
 __device__ __forceinline__ uint32_t sign_slots(const DiagEntry* d, int count, uint64_t base, uint32_t jt,
                                                uint32_t& touched) {
@@ -504,7 +512,7 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
     dep_lo[i] = A.dep[i];
     dep_hi[i] = A.dep[128 + i];
   }
-  // The pass's per-lane table lookups (ZZ phases and generator weights, phase entries) read
+  // The pass's per-lane table lookups (ZZ phases and generator weights) read
   // a copy of their ctab window in dynamic LDS.
   C* win = reinterpret_cast<C*>(qsv_dyn_lds);
   const int win_n = A.win_n;
@@ -544,9 +552,6 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
     }
   }
   asm volatile("" :: "v"(warm));
-  // bit q of the global index of local index j
-  auto gbit = [&](int j, int l, int q) -> int { return l >= 0 ? (j >> l) & 1 : (int)((base >> q) & 1); };
-
   double acc = 0.0;
   const TileOp* O = A.ops;
   for (int oi = 0; oi < A.n_ops; ++oi, ++O) {
@@ -749,49 +754,95 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
         apply_staged(v);
         if (ADJ) apply_staged(w);
       } else if (on && active && type == OP_DIAG && ob) {
-        // Slots two at a time, each pair walking the run's entries (scalar loads, cached):
-        // phases and generator weights for every slot at once would hold another register
-        // block and cut the number of resident waves.
+        // Entry by entry: one read of the entry, one of its two or four phases (and
+        // weights), then each slot times the phase that its own bits, its lane's and the
+        // tile's select.  The slots that share a phase go together, so an entry on a slot
+        // bit forms two phases and one on lanes or outside bits a single one per lane.
+        // Walking the run once per slot pair, with every index formed per slot and looked up
+        // per lane, took about 12 dependent reads per entry: 10-qubit ansatz with 80 angles
+        // 333 -> 254 us, 120 gates of every kind on 23 qubits in complex64 711 -> 500 us, 48
+        // uneven ansatz circuits 2977 -> 2400 us.
+        // Complex64 passes multiply a run's phases (and sum its weights) per slot first and then
+        // the amplitudes once; complex128 passes, where a second register block would cut the
+        // resident waves, multiply the amplitudes entry by entry.
+        constexpr bool gather = sizeof(R) == 4;
+        uint32_t flips = 0, touched = 0;
+        C ph[gather ? NR : 1];
+        double gws[gather && ADJ ? NR : 1];
 #pragma unroll
-        for (int k0 = 0; k0 < NR; k0 += 2) {
-          C ph[2] = {C{1, 0}, C{1, 0}};
-          double gw[2] = {0.0, 0.0};
-          uint32_t sm = 0;
-          for (int e = 0; e < count; ++e) {
-            const DiagEntry* d = A.diag + first + e;
-            const uint64_t ocm = ld(&d->ocmask);
-            if ((base & ocm) != ocm) continue;  // an outside control is 0 in this tile
-            const uint32_t lcm = ld(&d->lcmask);
-            if (ld(&d->kind) == DIAG_SIGN) {
-              const uint32_t tm = ld(&d->tmask);
-              if (((uint32_t)jt & tm) == tm) sm ^= ld(&d->kmask);
-            } else {
-              const int l0 = ld(&d->l0), l1 = ld(&d->l1), q0 = ld(&d->q0), q1 = ld(&d->q1);
-              const int mat = ld(&d->mat);
-              const int dg = ADJ ? ld(&d->gen) : -1;
-#pragma unroll
-              for (int h = 0; h < 2; ++h) {
-                const int j = jt | spread_of<NR>(reg_cur, k0 + h);
-                if (((uint32_t)j & lcm) != lcm) continue;
-                const int idx = gbit(j, l0, q0) | (q1 >= 0 ? gbit(j, l1, q1) << 1 : 0);
-                ph[h] = cmul(ph[h], tab(mat + idx));
-                if (ADJ && dg >= 0) gw[h] += (double)tab(dg + idx).x;
-              }
-            }
+        for (int k = 0; k < (gather ? NR : 0); ++k) {
+          ph[k] = C{1, 0};
+          if (ADJ) gws[k] = 0.0;
+        }
+        for (int e = 0; e < count; ++e) {
+          const PhaseFields f = ld_record(reinterpret_cast<const PhaseFields*>(&A.diag[first + e].ocmask));
+          if ((base & f.ocmask) != f.ocmask) continue;  // an outside control is 0 in this tile
+          const bool in = ((uint32_t)jt & f.tmask) == f.tmask;
+          if (f.where & kWhereSign) {
+            flips ^= in ? f.kmask : 0u;
+            touched |= f.kmask;
+            continue;
           }
+          const bool two = (f.where & kWhereTwo) != 0, grad = ADJ && f.gtab >= 0;
+          auto bit_at = [&](uint32_t src) -> bool {
+            return src < 32 ? ((uint32_t)jt >> src) & 1u : src < kNoBit && ((base >> (src - 32)) & 1);
+          };
+          const bool t0 = bit_at(f.where & 255u), t1 = bit_at((f.where >> 8) & 255u);
+          for (uint32_t u = 0; u < 4; ++u) {
+            if (((u & 1) && !f.bits0) || ((u & 2) && !f.bits1)) continue;
+            const uint32_t ks = f.kmask & ((u & 1) ? f.bits0 : ~f.bits0) & ((u & 2) ? f.bits1 : ~f.bits1);
+            // half of the table that a lane's second bit selects, then the entry its first does
+            const bool i0 = t0 || (u & 1), i1 = t1 || (u & 2);
+            C p = csel(i0, ldc(T + f.tab + 1), ldc(T + f.tab));
+            if (two) p = csel(i1, csel(i0, ldc(T + f.tab + 3), ldc(T + f.tab + 2)), p);
+            p = csel(in, p, C{1, 0});
+            double gw = 0.0;
+            if (grad) {
+              gw = (double)(i0 ? ldc(T + f.gtab + 1).x : ldc(T + f.gtab).x);
+              if (two) gw = i1 ? (double)(i0 ? ldc(T + f.gtab + 3).x : ldc(T + f.gtab + 2).x) : gw;
+            }
+            if constexpr (gather) {
+              const double gs = in ? gw : 0.0;
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int k = k0 + h;
-            C p = ph[h];
-            flip_sign(p, (sm << (31 - k)) & 0x80000000u);
-            if (ADJ) {
-              double g = gw[h] * im_conj_mul(w[k], v[k]);
-              cmul_in(w[k], p, g);
-              cmul_in(v[k], p, g);
-              acc += g;
-            } else {
+              for (int k = 0; k < NR; ++k) {
+                if (!((ks >> k) & 1u)) continue;
+                ph[k] = cmul(ph[k], p);
+                if (ADJ) gws[k] += gs;
+              }
+              continue;
+            }
+            if (grad) {
+              double g = 0.0;
+#pragma unroll
+              for (int k = 0; k < NR; ++k)
+                if ((ks >> k) & 1u) g += im_conj_mul(w[k], v[k]);
+              acc = __builtin_fma(in ? gw : 0.0, g, acc);
+            }
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+              if (!((ks >> k) & 1u)) continue;
+              if (ADJ) cmul_in(w[k], p);
               cmul_in(v[k], p);
             }
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+          const uint32_t f = (flips << (31 - k)) & 0x80000000u;
+          if constexpr (gather) {
+            flip_sign(ph[k], f);
+            if (ADJ) {
+              double g = gws[k] * im_conj_mul(w[k], v[k]);
+              cmul_in(w[k], ph[k], g);
+              cmul_in(v[k], ph[k], g);
+              acc += g;
+            } else {
+              cmul_in(v[k], ph[k]);
+            }
+          } else {
+            if (!((touched >> k) & 1u)) continue;
+            flip_sign(v[k], f);
+            if (ADJ) flip_sign(w[k], f);
           }
         }
       } else if (on && active && type == OP_ZZ) {

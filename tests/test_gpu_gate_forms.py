@@ -43,3 +43,39 @@ def test_controlled_x_moves_every_amplitude(dtype, n, tile):
         cm = sum(1 << c for c in g["ctrls"])
         ref = ref[np.where((x & cm) == cm, x ^ (1 << g["targets"][0]), x)]
     assert np.array_equal(_run(Q, circ, psi, dtype, tile), ref)
+
+
+def _phase_gates(n, count, rng, n_params):
+    gates = []
+    for _ in range(count):
+        kind = str(rng.choice(["RZ", "PS", "RZZ", "Z", "S", "T", "RX"]))
+        qs = rng.permutation(n)
+        nt = 2 if kind == "RZZ" else 1
+        nc = int(rng.integers(0, 3))
+        par = ()
+        if kind in ("RZ", "PS", "RZZ", "RX"):
+            par = ((int(rng.integers(0, n_params)), float(rng.choice([1.0, -0.5])), float(rng.uniform(-1, 1))),)
+        gates.append(W.gate(kind, tuple(qs[:nt]), ctrls=tuple(qs[nt:nt + nc]) if kind != "RX" else (), params=par))
+    return gates
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("n,tile,adj", [(9, 9, 9), (11, 9, 10), (13, 12, 10), (14, 10, 12)])
+def test_phase_runs_and_their_gradients(dtype, n, tile, adj):
+    """Runs of phases, sign flips and their gradients with targets and controls on slots,
+    lanes, waves and outside qubits."""
+    Q = _q()
+    rng = np.random.default_rng(100 + n)
+    circ = W.circuit(n, [W.gate("H", (q,)) for q in range(n)] + _phase_gates(n, 70, rng, 5))
+    params = rng.uniform(-np.pi, np.pi, 5)
+    ham = W.random_pauli_sum(n, 6, rng)
+    s = Q.qsv_state_create(n, dtype)
+    Q.qsv_state_set_option(s, Q.OPT_TILE_QUBITS, tile)
+    Q.qsv_state_set_option(s, Q.OPT_ADJ_TILE_QUBITS, adj)
+    e, g = Q.qsv_expectation_and_grad(s, circ, ham, params)
+    e0, g0 = O.grad_adjoint(circ, ham, params)
+    scale = max(1.0, sum(abs(c) for c, _ in ham))
+    assert abs(e - e0) <= TOL[dtype] * scale
+    assert np.max(np.abs(g - g0)) <= TOL[dtype] * scale
+    Q.qsv_apply_circuit(s, circ, params)
+    assert np.max(np.abs(Q.qsv_state_get(s) - O.simulate(circ, params))) <= TOL[dtype]
