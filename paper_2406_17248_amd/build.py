@@ -14,7 +14,7 @@ LIB = os.path.join(HERE, "libqsv.so")
 # type, direction and launch form, so that their instantiations build in parallel.
 SOURCES = [("tile_rb.hip", [f"-DQSV_RB_REAL={r}", f"-DQSV_RB_ADJ={a}", f"-DQSV_RB_MULTI={m}"])
            for r in ("double", "float") for a in ("true", "false") for m in (0, 1)]
-SOURCES += [(s, []) for s in ("tile_lds.hip", "qsv_kernels.hip", "engine.cpp", "api.cpp", "batch.cpp", "mpnn.hip",
+SOURCES += [(s, []) for s in ("tile_lds.hip", "qsv_kernels.hip", "pauli_multi.hip", "engine.cpp", "api.cpp", "batch.cpp", "mpnn.hip",
                               "noalloc.hip")]
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -309,6 +309,9 @@ void run_forward(qsv_state* s, const Plan& p, const Uploaded& u, void* psi, int6
 // Pauli-sum groups uploaded once per call.
 struct DevPauli {
   std::vector<PauliGroup> groups;
+  std::vector<PauliLaunch> launches;   // two result columns each
+  std::vector<const PauliMultiGroup*> mg;  // launches of several groups, else null
+  std::vector<const PauliMultiTerm*> mt;
   std::vector<const uint64_t*> z;
   std::vector<const double*> cre, cim;
   std::vector<const uint32_t*> pats;   // diagonal groups over >= 12 qubits, else null
@@ -348,14 +351,23 @@ void pattern_tables(PauliGroup& g, int n, std::vector<uint32_t>& pats, std::vect
   g = h;
 }
 
-// Bytes of the groups' term tables (z masks, coefficient real and imaginary parts, and for
-// qualifying diagonal groups the pattern tables, each array `align`-byte aligned).  Sorts
-// the terms of diagonal groups by pattern (pattern_tables).
-size_t pauli_table_bytes(std::vector<PauliGroup>& groups, int n, size_t align = 256) {
+// Bytes of the launches' tables (groups by themselves: z masks, coefficient real and
+// imaginary parts, and for qualifying diagonal groups the pattern tables; several groups in one
+// pass: their records), each array `align`-byte aligned.  Sorts the terms of diagonal groups
+// that run by themselves by pattern (pattern_tables).
+size_t pauli_table_bytes(std::vector<PauliGroup>& groups, const std::vector<PauliLaunch>& launches, int n,
+                         size_t align = 256) {
   size_t total = 0;
   std::vector<uint32_t> pats;
   std::vector<int32_t> rfirst;
-  for (auto& g : groups) {
+  for (const PauliLaunch& L : launches) {
+    if (L.kind != PL_GROUP) {
+      size_t nt = 0;
+      for (int32_t g : L.groups) nt += groups[g].zmasks.size();
+      total += align_up(L.groups.size() * sizeof(PauliMultiGroup), align) + align_up(nt * sizeof(PauliMultiTerm), align);
+      continue;
+    }
+    PauliGroup& g = groups[L.groups[0]];
     total += align_up(g.zmasks.size() * 8, align) * 3;
     pattern_tables(g, n, pats, rfirst);
     if (!pats.empty()) total += align_up(pats.size() * 4, align) + align_up(rfirst.size() * 4, align);
@@ -366,99 +378,143 @@ size_t pauli_table_bytes(std::vector<PauliGroup>& groups, int n, size_t align = 
 // Pack the tables into host bytes `host`; the returned pointers are where they sit once
 // the bytes are copied to device address `dev`.  The groups must have passed through
 // pauli_table_bytes (diagonal groups sorted).
-DevPauli pack_pauli(std::vector<PauliGroup> groups, int n, char* host, char* dev, size_t align = 256) {
+DevPauli pack_pauli(std::vector<PauliGroup> groups, std::vector<PauliLaunch> launches, int n, bool lambda, char* host,
+                    char* dev, size_t align = 256) {
   DevPauli dp;
   dp.groups = std::move(groups);
+  dp.launches = std::move(launches);
   size_t off = 0;
   std::vector<uint32_t> pats;
   std::vector<int32_t> rfirst;
-  for (auto& g : dp.groups) {
-    const size_t sz = g.zmasks.size() * 8, al = align_up(sz, align);
-    std::memcpy(host + off, g.zmasks.data(), sz);
-    std::memcpy(host + off + al, g.cre.data(), sz);
-    std::memcpy(host + off + 2 * al, g.cim.data(), sz);
-    dp.z.push_back(reinterpret_cast<const uint64_t*>(dev + off));
-    dp.cre.push_back(reinterpret_cast<const double*>(dev + off + al));
-    dp.cim.push_back(reinterpret_cast<const double*>(dev + off + 2 * al));
-    off += 3 * al;
-    pattern_tables(g, n, pats, rfirst);  // already sorted: this only rebuilds the tables
-    if (pats.empty()) {
-      dp.pats.push_back(nullptr);
-      dp.rfirst.push_back(nullptr);
-      dp.n_pats.push_back(0);
+  std::vector<PauliMultiGroup> mg;
+  std::vector<PauliMultiTerm> mt;
+  auto put = [&](const void* p, size_t bytes) {
+    char* at = dev + off;
+    std::memcpy(host + off, p, bytes);
+    off += align_up(bytes, align);
+    return at;
+  };
+  for (const PauliLaunch& L : dp.launches) {
+    dp.z.push_back(nullptr);
+    dp.cre.push_back(nullptr);
+    dp.cim.push_back(nullptr);
+    dp.pats.push_back(nullptr);
+    dp.rfirst.push_back(nullptr);
+    dp.n_pats.push_back(0);
+    dp.mg.push_back(nullptr);
+    dp.mt.push_back(nullptr);
+    if (L.kind != PL_GROUP) {
+      pauli_multi_tables(dp.groups, L, n, lambda, mg, mt);
+      dp.mg.back() = reinterpret_cast<const PauliMultiGroup*>(put(mg.data(), mg.size() * sizeof(PauliMultiGroup)));
+      dp.mt.back() = reinterpret_cast<const PauliMultiTerm*>(put(mt.data(), mt.size() * sizeof(PauliMultiTerm)));
       continue;
     }
-    std::memcpy(host + off, pats.data(), pats.size() * 4);
-    dp.pats.push_back(reinterpret_cast<const uint32_t*>(dev + off));
-    off += align_up(pats.size() * 4, align);
-    std::memcpy(host + off, rfirst.data(), rfirst.size() * 4);
-    dp.rfirst.push_back(reinterpret_cast<const int32_t*>(dev + off));
-    off += align_up(rfirst.size() * 4, align);
-    dp.n_pats.push_back((int32_t)pats.size());
+    PauliGroup& g = dp.groups[L.groups[0]];
+    const size_t sz = g.zmasks.size() * 8;
+    dp.z.back() = reinterpret_cast<const uint64_t*>(put(g.zmasks.data(), sz));
+    dp.cre.back() = reinterpret_cast<const double*>(put(g.cre.data(), sz));
+    dp.cim.back() = reinterpret_cast<const double*>(put(g.cim.data(), sz));
+    pattern_tables(g, n, pats, rfirst);  // already sorted: this only rebuilds the tables
+    if (pats.empty()) continue;
+    dp.pats.back() = reinterpret_cast<const uint32_t*>(put(pats.data(), pats.size() * 4));
+    dp.rfirst.back() = reinterpret_cast<const int32_t*>(put(rfirst.data(), rfirst.size() * 4));
+    dp.n_pats.back() = (int32_t)pats.size();
   }
   return dp;
 }
 
-DevPauli upload_pauli(qsv_state* s, const qsv_pauli_sum* h, DevBuf& buf) {
+// lambda: run_pauli will write H psi; costate: for a reverse sweep (complex64 then rounds its
+// partial sums in the order of the groups, whatever the size of the state).
+DevPauli upload_pauli(qsv_state* s, const qsv_pauli_sum* h, DevBuf& buf, bool lambda, bool costate) {
   std::vector<PauliGroup> groups = group_pauli_sum(h);
-  const size_t bytes = pauli_table_bytes(groups, s->n);
+  std::vector<PauliLaunch> launches = plan_pauli(groups, s->n, s->dtype, costate && s->dtype == QSV_C64);
+  const size_t bytes = pauli_table_bytes(groups, launches, s->n);
   const size_t total = bytes ? bytes : 256;
   char* st = static_cast<char*>(stage_acquire(s, total));
   buf.reserve(total);
-  DevPauli dp = pack_pauli(std::move(groups), s->n, st, static_cast<char*>(buf.p));
+  DevPauli dp = pack_pauli(std::move(groups), std::move(launches), s->n, lambda, st, static_cast<char*>(buf.p));
   hip_check(hipMemcpyAsync(buf.p, st, total, hipMemcpyHostToDevice, s->stream), "upload pauli");
   stage_release_after_queue(s);
   return dp;
 }
 
-// Expectation partials (and optionally lambda = H psi) for batch states; returns the device
-// pointer of reduced columns [batch][2 * groups] in s->outbuf at byte offset out_off.
-// partials: NULL for the state's workspace (all groups at once), or a caller's buffer of
-// 2 * chunk * pauli_blocks(n) doubles that groups reuse `chunk` at a time, each chunk's
+// Workgroups per launch (the partial columns' length) of a planned Pauli sum.
+unsigned pauli_grid(const std::vector<PauliLaunch>& launches, int n) {
+  for (const PauliLaunch& L : launches)
+    if (L.kind != PL_GROUP) return std::max(pauli_blocks(n), pauli_multi_blocks(n));
+  return pauli_blocks(n);
+}
+
+// Expectation partials (and optionally lambda = H psi) for batch states; writes the reduced
+// columns [batch][2 * launches] to out_cols.
+// partials: NULL for the state's workspace (all launches at once), or a caller's buffer of
+// 2 * chunk * pauli_grid() doubles that launches reuse `chunk` at a time, each chunk's
 // columns reduced before the next chunk starts (batch 1 only; the same sums in the same
 // order).  untimed: launch without profiling events.
 void run_pauli(qsv_state* s, const DevPauli& dp, const void* psi, void* lam, int64_t bstride, int batch,
                double* out_cols, double* partials = nullptr, int chunk = 0, bool untimed = false) {
-  const int G = (int)dp.groups.size();
-  const unsigned nblk = pauli_blocks(s->n);
+  const int NL = (int)dp.launches.size();
+  const unsigned nblk = pauli_grid(dp.launches, s->n);
   if (!partials) {
-    const size_t need = (size_t)batch * 2 * G * nblk * sizeof(double);
+    const size_t need = (size_t)batch * 2 * NL * nblk * sizeof(double);
     s->partials.reserve(need ? need : 8);
     partials = static_cast<double*>(s->partials.p);
-    chunk = G;
-  } else if (chunk < 1 || (batch != 1 && chunk < G)) {
+    chunk = NL;
+  } else if (chunk < 1 || (batch != 1 && chunk < NL)) {
     fail(QSV_EINVAL, "internal: chunked Pauli partials need batch 1");
   }
-  if (lam && G == 0)
+  if (lam && NL == 0)
     hip_check(launch_set_basis(s->dtype, lam, bstride, batch, s->n, ~0ull, s->stream), "zero lambda");
-  for (int g0 = 0; g0 < G; g0 += chunk) {
-  const int g1 = std::min(G, g0 + chunk), nc = 2 * (g1 - g0);
-  for (int g = g0; g < g1; ++g) {
-    PauliGroupArgs A{};
-    A.psi = psi;
-    A.lam = lam;
-    A.bstride = bstride;
-    A.zmasks = dp.z[g];
-    A.cre = dp.cre[g];
-    A.cim = dp.cim[g];
-    A.partials = partials;
-    A.xmask = dp.groups[g].xmask;
-    A.n_terms = (int32_t)dp.groups[g].zmasks.size();
-    A.n_qubits = s->n;
-    A.accumulate = g > 0 ? 1 : 0;
-    A.col = 2 * (g - g0);
-    A.ncols = nc;
-    A.real_coeffs = std::all_of(dp.groups[g].cim.begin(), dp.groups[g].cim.end(), [](double c) { return c == 0.0; });
-    A.pats = dp.pats[g];
-    A.rfirst = dp.rfirst[g];
-    A.n_pats = dp.n_pats[g];
-    // read psi; write lambda (and read it when accumulating)
-    const double sb = (double)batch * (double)s->namps() * (double)s->amp_bytes();
-    const double bytes = sb * (1.0 + (lam ? 1.0 : 0.0) + (lam && g > 0 ? 1.0 : 0.0));
-    if (untimed) hip_check(launch_pauli_group(s->dtype, A, batch, s->stream), "pauli pass");
-    else timed(s, QSV_K_PAULI, bytes, [&] { return launch_pauli_group(s->dtype, A, batch, s->stream); }, "pauli pass");
-  }
-  hip_check(launch_reduce_columns(partials, nblk, (int64_t)batch * nc, out_cols + 2 * g0, s->stream), "reduce");
+  for (int l0 = 0; l0 < NL; l0 += chunk) {
+    const int l1 = std::min(NL, l0 + chunk), nc = 2 * (l1 - l0);
+    for (int l = l0; l < l1; ++l) {
+      const PauliLaunch& L = dp.launches[l];
+      const auto launch = [&]() -> hipError_t {
+        if (L.kind != PL_GROUP) {
+          PauliMultiArgs A{};
+          A.psi = psi;
+          A.lam = lam;
+          A.bstride = bstride;
+          A.groups = dp.mg[l];
+          A.terms = dp.mt[l];
+          A.partials = partials;
+          A.tile = L.tile;
+          A.n_groups = (int32_t)L.groups.size();
+          A.n_qubits = s->n;
+          A.accumulate = l > 0 ? 1 : 0;
+          A.col = 2 * (l - l0);
+          A.ncols = nc;
+          return L.kind == PL_TILE ? launch_pauli_tile(s->dtype, A, nblk, batch, s->stream)
+                                   : launch_pauli_gather(s->dtype, A, nblk, batch, s->stream);
+        }
+        const PauliGroup& g = dp.groups[L.groups[0]];
+        PauliGroupArgs A{};
+        A.psi = psi;
+        A.lam = lam;
+        A.bstride = bstride;
+        A.zmasks = dp.z[l];
+        A.cre = dp.cre[l];
+        A.cim = dp.cim[l];
+        A.partials = partials;
+        A.xmask = g.xmask;
+        A.n_terms = (int32_t)g.zmasks.size();
+        A.n_qubits = s->n;
+        A.accumulate = l > 0 ? 1 : 0;
+        A.col = 2 * (l - l0);
+        A.ncols = nc;
+        A.real_coeffs = std::all_of(g.cim.begin(), g.cim.end(), [](double c) { return c == 0.0; });
+        A.pats = dp.pats[l];
+        A.rfirst = dp.rfirst[l];
+        A.n_pats = dp.n_pats[l];
+        return launch_pauli_group(s->dtype, A, nblk, batch, s->stream);
+      };
+      // read psi; write lambda (and read it when accumulating)
+      const double sb = (double)batch * (double)s->namps() * (double)s->amp_bytes();
+      const double bytes = sb * (1.0 + (lam ? 1.0 : 0.0) + (lam && l > 0 ? 1.0 : 0.0));
+      if (untimed) hip_check(launch(), "pauli pass");
+      else timed(s, QSV_K_PAULI, bytes, launch, "pauli pass");
+    }
+    hip_check(launch_reduce_columns(partials, nblk, (int64_t)batch * nc, out_cols + 2 * l0, s->stream), "reduce");
   }
 }
 
@@ -522,8 +578,8 @@ void energies_and_grads(qsv_state* s, const qsv_circuit* c, const qsv_pauli_sum*
     UploadReq req = {adj, ctab_adj, batch};
     upload_plans(s, &req, 1, &up[1]);
   }
-  DevPauli dp = upload_pauli(s, h, s->pauli);
-  const int G = (int)dp.groups.size();
+  DevPauli dp = upload_pauli(s, h, s->pauli, adj != nullptr, adj != nullptr);
+  const int G = (int)dp.launches.size();
   if (run_fwd) run_forward(s, fwd, up[0], s->ws_psi.p, bstride, s->psi, 0, batch);
   // output columns: energies [batch][2G] then gradient slots [batch][P]
   const int P = adj ? adj->n_pslots : 0;
@@ -794,8 +850,8 @@ int qsv_expectation(qsv_state* s, const qsv_pauli_sum* h, double* out_re, double
     check_state(s);
     validate_pauli_sum(h, s->n);
     set_device(s);
-    DevPauli dp = upload_pauli(s, h, s->pauli);
-    const int G = (int)dp.groups.size();
+    DevPauli dp = upload_pauli(s, h, s->pauli, false, false);
+    const int G = (int)dp.launches.size();
     s->outbuf.reserve((2 * G + 1) * sizeof(double));
     run_pauli(s, dp, s->psi, nullptr, 0, 1, static_cast<double*>(s->outbuf.p));
     double* host = static_cast<double*>(stage_acquire(s, (2 * G + 1) * sizeof(double)));
@@ -817,17 +873,18 @@ int qsv_expectation_noalloc(qsv_state* s, const qsv_pauli_sum* h, double* out_re
     set_device(s);
     char* scr = static_cast<char*>(noalloc_scratch());
     std::vector<PauliGroup> groups = group_pauli_sum(h);
-    const int G = (int)groups.size();
+    std::vector<PauliLaunch> launches = plan_pauli(groups, s->n, s->dtype, false);
+    const int G = (int)launches.size();
     double re = 0, im = 0;
     if (G > 0) {
-      // scratch layout: term tables | reduced columns | partials of kNoallocChunk groups
-      const size_t tab = pauli_table_bytes(groups, s->n, 8);
+      // scratch layout: term tables | reduced columns | partials of kNoallocChunk launches
+      const size_t tab = pauli_table_bytes(groups, launches, s->n, 8);
       const size_t out_off = align_up(tab, 256);
       const size_t part_off = align_up(out_off + (size_t)2 * G * sizeof(double), 256);
-      const size_t part_bytes = (size_t)2 * kNoallocChunk * pauli_blocks(s->n) * sizeof(double);
+      const size_t part_bytes = (size_t)2 * kNoallocChunk * pauli_grid(launches, s->n) * sizeof(double);
       if (part_off + part_bytes > kNoallocScratchBytes) fail(QSV_ERANGE, "Pauli sum too large for the fixed scratch");
       std::vector<char> host(tab);
-      DevPauli dp = pack_pauli(std::move(groups), s->n, host.data(), scr, 8);
+      DevPauli dp = pack_pauli(std::move(groups), std::move(launches), s->n, false, host.data(), scr, 8);
       hip_check(hipMemcpyAsync(scr, host.data(), tab, hipMemcpyHostToDevice, s->stream), "upload pauli");
       double* d_out = reinterpret_cast<double*>(scr + out_off);
       run_pauli(s, dp, s->psi, nullptr, 0, 1, d_out, reinterpret_cast<double*>(scr + part_off), kNoallocChunk, true);
@@ -852,8 +909,8 @@ int qsv_apply_pauli_sum(qsv_state* dst, const qsv_state* src, const qsv_pauli_su
     validate_pauli_sum(h, dst->n);
     set_device(dst);
     ++dst->generation;
-    DevPauli dp = upload_pauli(dst, h, dst->pauli);
-    const int G = (int)dp.groups.size();
+    DevPauli dp = upload_pauli(dst, h, dst->pauli, true, false);
+    const int G = (int)dp.launches.size();
     dst->outbuf.reserve((2 * G + 1) * sizeof(double));
     run_pauli(dst, dp, src->psi, dst->psi, 0, 1, static_cast<double*>(dst->outbuf.p));
     hip_check(hipStreamSynchronize(dst->stream), "hipStreamSynchronize");
@@ -1033,8 +1090,8 @@ int qsv_expectation_general(qsv_state* psi, const qsv_circuit* c_r, const double
     run_forward(s, fr, up[map[0]], P1, bs, psi->psi, 0, 2);
     if (fl) run_forward(s, *fl, up[map[2]], P2, bs, phi->psi, 0, 2);
     else hip_check(launch_broadcast_state(s->dtype, P2, bs, 2, phi->psi, s->n, s->stream), "copy phi");
-    DevPauli dp = upload_pauli(s, h, s->pauli);
-    const int G = (int)dp.groups.size();
+    DevPauli dp = upload_pauli(s, h, s->pauli, true, true);
+    const int G = (int)dp.launches.size();
     const int Pr = ar ? ar->n_pslots : 0, Pl = al ? al->n_pslots : 0;
     const size_t o_tmp = 0, o_E = 2 * (size_t)G, o_r = o_E + 2, o_l = o_r + 2 * (size_t)Pr, total = o_l + 2 * (size_t)Pl;
     s->outbuf.reserve((total + 1) * sizeof(double));
@@ -1112,10 +1169,10 @@ int qsv_expectation_and_grad_multi(qsv_state* s, const qsv_circuit* c, const qsv
     double* d_out = static_cast<double*>(s->outbuf.p);
     size_t col = 0;
     for (size_t k = 0; k < n_hams; ++k) {
-      DevPauli dp = upload_pauli(s, &hams[k], s->pauli);
-      ngroups[k] = (int)dp.groups.size();
+      DevPauli dp = upload_pauli(s, &hams[k], s->pauli, true, true);
+      ngroups[k] = (int)dp.launches.size();
       run_pauli(s, dp, P + k * one, L + k * one, bs, 1, d_out + col);
-      col += 2 * dp.groups.size();
+      col += 2 * dp.launches.size();
     }
     run_adjoint(s, adj, up[1], P, L, bs, (int)n_hams, d_out + ecols);
     double* host = static_cast<double*>(stage_acquire(s, (ecols + n_hams * (size_t)Pn + 1) * sizeof(double)));

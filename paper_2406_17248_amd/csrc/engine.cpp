@@ -1750,4 +1750,149 @@ std::vector<PauliGroup> group_pauli_sum(const qsv_pauli_sum* h) {
   return groups;
 }
 
+namespace {
+
+// Diagonal groups of more terms than this run by themselves where their pattern pass applies
+// (n >= 12): it costs a term a few operations per 4096 amplitudes, a pass over several groups
+// a few per amplitude.
+constexpr size_t kMergedDiagTerms = 32;
+// From this many qubits on (complex64, complex128: states of 128 MiB), tiles through LDS; below
+// it one gathering launch, whose partners the caches hold.  Microseconds per call, tiles against
+// gathering: 50 random 1-4-local terms, complex128, expectation 22 qubits 164 / 140, 23 257 /
+// 309, 25 814 / 1445, H psi 22 227 / 172, 23 372 / 430, 25 1724 / 2487; complex64, expectation
+// 23 267 / 230, 24 407 / 394, 25 730 / 823, H psi 23 310 / 274, 24 513 / 573, 25 1022 / 1137.
+constexpr int kPauliTileMin[2] = {24, 23};
+constexpr int kTileSeeds = 8;
+
+}  // namespace
+
+std::vector<PauliLaunch> plan_pauli(const std::vector<PauliGroup>& groups, int32_t n, int32_t dtype, bool in_order) {
+  std::vector<PauliLaunch> out;
+  const int G = (int)groups.size();
+  auto alone = [&](int g) {
+    PauliLaunch L;
+    L.kind = PL_GROUP;
+    L.groups = {g};
+    out.push_back(std::move(L));
+  };
+  if (G == 1) {
+    alone(0);
+    return out;
+  }
+  auto big_diagonal = [&](int g) {
+    return groups[g].xmask == 0 && n >= 12 && groups[g].zmasks.size() > kMergedDiagTerms;
+  };
+  const int cls = dtype == QSV_C64 ? 0 : 1;
+  if (n < kPauliTileMin[cls] || in_order) {
+    PauliLaunch cur;
+    cur.kind = PL_GATHER;
+    auto close = [&] {
+      if (cur.groups.size() == 1) alone(cur.groups[0]);
+      else if (!cur.groups.empty()) out.push_back(cur);
+      cur.groups.clear();
+    };
+    for (int g = 0; g < G; ++g) {
+      if (big_diagonal(g)) {
+        close();
+        alone(g);
+      } else {
+        cur.groups.push_back(g);
+      }
+    }
+    close();
+    return out;
+  }
+  // tiles: repeatedly the tile that covers most of the groups left, grown from a seed group by
+  // the group that needs the fewest further qubits
+  const int m = kPauliTileQubits, low = dtype == QSV_C64 ? 4 : 3;
+  const uint64_t lowm = (1ull << low) - 1;
+  std::vector<int32_t> rem, single;
+  for (int g = 0; g < G; ++g) {
+    if (big_diagonal(g) || popc(groups[g].xmask | lowm) > m) single.push_back(g);
+    else rem.push_back(g);
+  }
+  while (!rem.empty()) {
+    std::vector<int32_t> best;
+    uint64_t best_T = 0;
+    const int seeds = rem.size() <= 256 ? std::min<int>(kTileSeeds, (int)rem.size()) : 1;
+    for (int sd = 0; sd < seeds; ++sd) {
+      uint64_t T = lowm | groups[rem[(size_t)sd * rem.size() / seeds]].xmask;
+      std::vector<char> in(rem.size(), 0);
+      std::vector<int32_t> got;
+      for (;;) {
+        int next = -1, need = 99;
+        for (size_t i = 0; i < rem.size(); ++i) {
+          if (in[i]) continue;
+          const int k = popc(groups[rem[i]].xmask & ~T);
+          if (k == 0) {
+            in[i] = 1;
+            got.push_back(rem[i]);
+          } else if (k < need && popc(T) + k <= m) {
+            need = k;
+            next = (int)i;
+          }
+        }
+        if (next < 0) break;
+        T |= groups[rem[next]].xmask;
+      }
+      if (got.size() > best.size()) {
+        best = got;
+        best_T = T;
+      }
+    }
+    for (int q = 0; popc(best_T) < m; ++q) best_T |= 1ull << q;
+    PauliLaunch L;
+    L.kind = PL_TILE;
+    L.tile = best_T;
+    // (qubits added to fill the tile may cover further groups)
+    std::vector<int32_t> left;
+    for (int32_t g : rem) ((groups[g].xmask & ~best_T) == 0 ? L.groups : left).push_back(g);
+    rem.swap(left);
+    if (L.groups.size() == 1) alone(L.groups[0]);
+    else out.push_back(std::move(L));
+  }
+  for (int32_t g : single) alone(g);
+  return out;
+}
+
+void pauli_multi_tables(const std::vector<PauliGroup>& groups, const PauliLaunch& L, int32_t n, bool lambda,
+                        std::vector<PauliMultiGroup>& mg, std::vector<PauliMultiTerm>& mt) {
+  mg.clear();
+  mt.clear();
+  auto local = [&](uint64_t v) {  // the tile qubits of v as local bits
+    uint64_t r = 0, T = L.tile;
+    for (int b = 0; T; ++b, T &= T - 1)
+      if (v & T & (~T + 1)) r |= 1ull << b;
+    return r;
+  };
+  // the bits of the output index that the slot holds, counted from the top
+  const int bits = L.kind == PL_TILE ? kPauliTileQubits : n;
+  const int slots = L.kind == PL_TILE ? kPauliTileQubits - kPauliTileThreadBits : (n >= kPauliGatherFour ? 2 : 0);
+  for (int32_t g : L.groups) {
+    const PauliGroup& P = groups[g];
+    PauliMultiGroup M{};
+    M.x = L.kind == PL_TILE ? local(P.xmask) : P.xmask;
+    M.first = (int32_t)mt.size();
+    // the highest bit of x, where whole waves or slots share it
+    if (!lambda && M.x >> 6) M.half = 1ull << (63 - __builtin_clzll(M.x));
+    for (int im = 0; im < 2; ++im)
+      for (size_t k = 0; k < P.zmasks.size(); ++k) {
+        // i^{popcount(x & z)}: even counts real, odd ones imaginary (whatever the coefficient)
+        if ((popc(P.xmask & P.zmasks[k]) & 1) != im) continue;
+        PauliMultiTerm t{};
+        const uint64_t z = P.zmasks[k];
+        t.c = im ? P.cim[k] : P.cre[k];
+        if (popc(P.xmask & z) & 1) t.c = -t.c;
+        if (M.half) t.c *= 2.0;
+        const uint64_t lz = L.kind == PL_TILE ? local(z) : z;
+        t.zo = L.kind == PL_TILE ? z & ~L.tile : 0;
+        t.zt = (uint32_t)(lz & ((1ull << (bits - slots)) - 1));
+        t.pat = (uint32_t)(lz >> (bits - slots));
+        mt.push_back(t);
+        ++(im ? M.n_im : M.n_re);
+      }
+    mg.push_back(M);
+  }
+}
+
 }  // namespace qsv

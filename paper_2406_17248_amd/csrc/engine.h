@@ -279,4 +279,18 @@ struct PauliGroup {
 };
 std::vector<PauliGroup> group_pauli_sum(const qsv_pauli_sum* h);
 
+// The launches that evaluate a Pauli sum: one group by itself (pauli_group), or several in one
+// pass (pauli_gather, pauli_tile).
+enum PauliLaunchKind : int32_t { PL_GROUP = 0, PL_GATHER = 1, PL_TILE = 2 };
+struct PauliLaunch {
+  int32_t  kind;
+  uint64_t tile = 0;            // PL_TILE: the tile qubits
+  std::vector<int32_t> groups;  // indices of the groups, in order
+};
+// Every group in exactly one launch.  in_order: the groups add to H psi in their order.
+std::vector<PauliLaunch> plan_pauli(const std::vector<PauliGroup>& groups, int32_t n, int32_t dtype, bool in_order);
+// The group and term records of a PL_GATHER / PL_TILE launch; lambda: H psi is written.
+void pauli_multi_tables(const std::vector<PauliGroup>& groups, const PauliLaunch& L, int32_t n, bool lambda,
+                        std::vector<PauliMultiGroup>& mg, std::vector<PauliMultiTerm>& mt);
+
 }  // namespace qsv

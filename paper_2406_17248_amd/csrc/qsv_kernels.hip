@@ -584,8 +584,8 @@ void launch_pauli_mode(const PauliGroupArgs& A, dim3 grid, hipStream_t s) {
   else pauli_group<R, PG_DIAG><<<grid, 256, 0, s>>>(A);
 }
 
-hipError_t launch_pauli_group(int dtype, const PauliGroupArgs& A, int batch, hipStream_t s) {
-  const dim3 grid(pauli_blocks(A.n_qubits), (unsigned)batch);
+hipError_t launch_pauli_group(int dtype, const PauliGroupArgs& A, unsigned blocks, int batch, hipStream_t s) {
+  const dim3 grid(blocks, (unsigned)batch);
   if (dtype == 0) launch_pauli_mode<float>(A, grid, s);
   else launch_pauli_mode<double>(A, grid, s);
   return hipGetLastError();

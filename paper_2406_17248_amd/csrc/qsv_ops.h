@@ -224,4 +224,42 @@ struct PauliGroupArgs {
 };
 constexpr int kPauliMaxPatterns = 256;
 
+// Passes over several groups of terms (pauli_multi.hip).  x: the group's x mask (pauli_tile:
+// in tile-local bits); terms [first, first + n_re) have real factors, the next n_im imaginary
+// ones.
+// half (expectation only; 0: none): a bit of x that is the same across a wave.  The outputs
+// with that bit set are left out, and the coefficients count twice: f(y) psi[y ^ x] conj(psi[y])
+// and its partner's term are complex conjugates.
+struct PauliMultiGroup {
+  uint64_t x, half;
+  int32_t  first, n_re, n_im, pad;
+};
+// One term: coefficient (its i^{popcount(x & z)} taken out, the sign of z on x folded in) and
+// z split over the output index: the thread's bits, the bits outside it, and the slot's bits.
+struct PauliMultiTerm {
+  double   c;
+  uint64_t zo;
+  uint32_t zt, pat;
+};
+struct PauliMultiArgs {
+  const void*  psi;
+  void*        lam;           // output H psi (or NULL for expectation only)
+  int64_t      bstride;
+  const PauliMultiGroup* groups;
+  const PauliMultiTerm*  terms;
+  double*      partials;      // as PauliGroupArgs
+  uint64_t     tile;          // pauli_tile: the tile qubits
+  int32_t      n_groups;
+  int32_t      n_qubits;
+  int32_t      accumulate;
+  int32_t      col, ncols;
+  int32_t      splits;        // pauli_gather: workgroups sharing a chunk's groups (set at launch)
+};
+// pauli_tile: tile qubits and thread bits (eight slots per thread; 32 and 64 KiB of LDS for
+// complex64 and complex128).  pauli_gather: four outputs per thread from kPauliGatherFour
+// qubits on, one below.
+constexpr int kPauliTileQubits = 12;
+constexpr int kPauliTileThreadBits = 9;
+constexpr int kPauliGatherFour = 18;
+
 }  // namespace qsv

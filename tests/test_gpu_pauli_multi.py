@@ -1,0 +1,69 @@
+"""Pauli sums with several x masks in one pass, against the oracle (small states) and against the
+same sum one group at a time (states large enough for tiles)."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import statevector as O
+
+pytestmark = pytest.mark.gpu
+TOL = {"c64": 1e-5, "c128": 1e-12}
+
+
+@pytest.fixture(scope="module")
+def Q():
+    import paper_2406_17248_amd as Q
+    Q.lib()
+    return Q
+
+
+def _sum(n, terms, rng, diag=0):
+    h = W.random_pauli_sum(n, terms, rng, max_locality=min(n, 4))
+    h += [(float(rng.standard_normal()), tuple((int(q), "Z") for q in rng.permutation(n)[:2])) for _ in range(diag)]
+    if n > 6:  # every qubit at once, and both coefficient classes on one x mask
+        h += [(0.7, tuple((q, "XYZ"[q % 3]) for q in range(n))), (-0.3, ((0, "X"), (n - 1, "Y"))),
+              (0.2, ((0, "X"), (n - 1, "X")))]
+    return [h[i] for i in rng.permutation(len(h))]
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("n,terms,diag", [(1, 3, 0), (2, 6, 0), (5, 30, 5), (6, 3, 0), (8, 40, 0), (9, 1, 1),
+                                          (11, 50, 3), (12, 30, 50), (13, 9, 2), (17, 25, 0), (18, 21, 3)])
+def test_gathered_groups(Q, dtype, n, terms, diag):
+    rng = np.random.default_rng(1000 * n + terms)
+    h = _sum(n, terms, rng, diag)
+    psi = W.random_state(n, rng, np.complex64 if dtype == "c64" else np.complex128)
+    s, d = Q.qsv_state_create(n, dtype), Q.qsv_state_create(n, dtype)
+    Q.qsv_state_set(s, psi)
+    ref = O.apply_pauli_sum(psi.astype(np.complex128), n, h)
+    scale = max(1.0, sum(abs(c) for c, _ in h))
+    e = Q.qsv_expectation(s, h)
+    assert abs(e - np.vdot(psi.astype(np.complex128), ref)) <= TOL[dtype] * scale
+    assert Q.qsv_expectation_noalloc(s, h) == e
+    Q.qsv_apply_pauli_sum(d, s, h)
+    assert np.max(np.abs(Q.qsv_state_get(d) - ref)) <= TOL[dtype] * scale
+
+
+@pytest.mark.parametrize("dtype,n", [("c64", 23), ("c64", 24), ("c128", 22), ("c128", 23)])
+def test_tiled_groups_match_one_group_at_a_time(Q, dtype, n):
+    import torch
+    from paper_2406_17248_amd import torch_layer as TL
+    rng = np.random.default_rng(n)
+    h = _sum(n, 24, rng, 3) + [(0.4, ((q, p), (q + 1, p))) for q in range(n - 1) for p in "XYZ"]
+    cdt = torch.complex64 if dtype == "c64" else torch.complex128
+    g = torch.Generator(device="cuda").manual_seed(n)
+    a = torch.randn(1 << n, generator=g, device="cuda", dtype=cdt)
+    a /= torch.linalg.vector_norm(a)
+    b, one = torch.empty_like(a), torch.empty_like(a)
+    s, d, t = TL.state_from_tensor(a), TL.state_from_tensor(b), TL.state_from_tensor(one)
+    Q.qsv_apply_pauli_sum(d, s, h)
+    e = Q.qsv_expectation(s, h)
+    ref = torch.zeros(1 << n, dtype=torch.complex128, device="cuda")
+    e_ref = 0.0
+    for term in h:
+        Q.qsv_apply_pauli_sum(t, s, [term])
+        ref += one
+        e_ref += Q.qsv_expectation(s, [term]).real
+    scale = max(1.0, sum(abs(c) for c, _ in h))
+    assert abs(e - e_ref) <= TOL[dtype] * scale
+    assert float((b - ref).abs().max()) <= TOL[dtype] * scale
