@@ -58,7 +58,9 @@ struct qsv_state {
   // includes `generation`, which every entry point that writes the amplitudes bumps
   std::string fwd_token;
   uint64_t generation = 0;
-  std::unordered_map<std::string, std::unique_ptr<Plan>> plans;
+  // by structure key, with the number of its last use
+  std::unordered_map<std::string, std::pair<std::unique_ptr<Plan>, uint64_t>> plans;
+  uint64_t plan_use = 0;
 
   size_t amp_bytes() const { return dtype == QSV_C64 ? 8 : 16; }
   uint64_t namps() const { return 1ull << n; }
@@ -138,20 +140,24 @@ void default_options(qsv_state* s) {
   s->opt[QSV_OPT_RELAYOUT] = 1;
 }
 
-PlanOptions plan_options(const qsv_state* s, bool adjoint, bool fuse_zz, bool relayout = false) {
+// batch: items that a launch runs.
+PlanOptions plan_options(const qsv_state* s, bool adjoint, bool fuse_zz, size_t batch, bool relayout = false) {
   return state_plan_options(s->dtype, s->n, (int32_t)s->opt[QSV_OPT_TILE_QUBITS],
-                            (int32_t)s->opt[QSV_OPT_ADJ_TILE_QUBITS], adjoint, fuse_zz, relayout);
+                            (int32_t)s->opt[QSV_OPT_ADJ_TILE_QUBITS], adjoint, fuse_zz, relayout, batch);
 }
 
-const Plan& get_plan(qsv_state* s, const qsv_circuit* c, bool adjoint, bool fuse_zz, bool relayout = false) {
-  const PlanOptions o = plan_options(s, adjoint, fuse_zz, relayout);
+const Plan& get_plan(qsv_state* s, const qsv_circuit* c, bool adjoint, bool fuse_zz, size_t batch,
+                     bool relayout = false) {
+  const PlanOptions o = plan_options(s, adjoint, fuse_zz, batch, relayout);
   std::string key = structure_key(c, adjoint, o);
-  auto it = s->plans.find(key);
-  if (it != s->plans.end()) return *it->second;
-  if (s->plans.size() > 64) s->plans.clear();
-  auto p = std::make_unique<Plan>(build_plan(c, adjoint, o));
-  const Plan& ref = *p;
-  s->plans.emplace(std::move(key), std::move(p));
+  auto& held = s->plans[std::move(key)];
+  held.second = ++s->plan_use;
+  if (held.first) return *held.first;
+  held.first = std::make_unique<Plan>(build_plan(c, adjoint, o));
+  const Plan& ref = *held.first;
+  if (s->plans.size() > 64)  // (a call holds up to four)
+    for (auto it = s->plans.begin(); it != s->plans.end();)
+      it = it->second.second + 8 < s->plan_use ? s->plans.erase(it) : std::next(it);
   return ref;
 }
 
@@ -814,7 +820,7 @@ int qsv_apply_circuit(qsv_state* s, const qsv_circuit* c, const double* params, 
     bool relay = s->opt[QSV_OPT_RELAYOUT] != 0 && !s->relay_failed;
     if (relay) {
       // relayout only pays when the plan has several register-blocked passes
-      const Plan& probe = get_plan(s, c, false, true, true);
+      const Plan& probe = get_plan(s, c, false, true, 1, true);
       relay = probe.relayout;
       const size_t need = s->namps() * s->amp_bytes();
       if (relay && s->relay.bytes < need) {
@@ -835,7 +841,7 @@ int qsv_apply_circuit(qsv_state* s, const qsv_circuit* c, const double* params, 
         }
       }
     }
-    const Plan& p = get_plan(s, c, false, true, relay);
+    const Plan& p = get_plan(s, c, false, true, 1, relay);
     std::vector<cplx> ctab(p.ctab_size);
     bind_ctab(p, c, params, nullptr, 0, ctab.data());
     Uploaded u;
@@ -934,8 +940,8 @@ int qsv_expectation_and_grad_batch(qsv_state* s, const qsv_circuit* c, const qsv
   return guarded([&] {
     batch_common(s, c, h, params, batch, n_params, out_E);
     if (n_params && !out_grad) fail(QSV_EINVAL, "out_grad is NULL");
-    const Plan& fwd = get_plan(s, c, false, true);
-    const Plan& adj = get_plan(s, c, true, true);
+    const Plan& fwd = get_plan(s, c, false, true, batch);
+    const Plan& adj = get_plan(s, c, true, true, batch);
     std::vector<cplx> cf((size_t)batch * fwd.ctab_size), ca((size_t)batch * adj.ctab_size);
     for (size_t b = 0; b < batch; ++b) {
       bind_ctab(fwd, c, params + b * n_params, nullptr, 0, cf.data() + b * fwd.ctab_size);
@@ -961,7 +967,7 @@ int qsv_expectation_batch(qsv_state* s, const qsv_circuit* c, const qsv_pauli_su
                           size_t batch, size_t n_params, double* out_E) {
   return guarded([&] {
     batch_common(s, c, h, params, batch, n_params, out_E);
-    const Plan& fwd = get_plan(s, c, false, true);
+    const Plan& fwd = get_plan(s, c, false, true, batch);
     std::vector<cplx> cf((size_t)batch * fwd.ctab_size);
     for (size_t b = 0; b < batch; ++b)
       bind_ctab(fwd, c, params + b * n_params, nullptr, 0, cf.data() + b * fwd.ctab_size);
@@ -971,7 +977,7 @@ int qsv_expectation_batch(qsv_state* s, const qsv_circuit* c, const qsv_pauli_su
 
 static std::string forward_token(const qsv_state* s, const qsv_circuit* c, const qsv_pauli_sum* h,
                                  const double* params, size_t batch, size_t n_params) {
-  std::string t = structure_key(c, false, plan_options(s, false, true));
+  std::string t = structure_key(c, false, plan_options(s, false, true, batch));
   auto put = [&](const void* p, size_t n) { if (n) t.append(reinterpret_cast<const char*>(p), n); };
   for (size_t i = 0; i < c->n_gates; ++i) {
     put(c->gates[i].param_coeff, sizeof(double) * 3);
@@ -993,7 +999,7 @@ int qsv_forward_batch(qsv_state* s, const qsv_circuit* c, const qsv_pauli_sum* h
                       size_t n_params, double* out_E) {
   return guarded([&] {
     batch_common(s, c, h, params, batch, n_params, out_E);
-    const Plan& fwd = get_plan(s, c, false, true);
+    const Plan& fwd = get_plan(s, c, false, true, batch);
     std::vector<cplx> cf((size_t)batch * fwd.ctab_size);
     for (size_t b = 0; b < batch; ++b)
       bind_ctab(fwd, c, params + b * n_params, nullptr, 0, cf.data() + b * fwd.ctab_size);
@@ -1011,8 +1017,8 @@ int qsv_backward_batch(qsv_state* s, const qsv_circuit* c, const qsv_pauli_sum* 
     if (!dE_weights) fail(QSV_EINVAL, "dE_weights is NULL");
     for (size_t b = 0; b < batch; ++b)
       if (!std::isfinite(dE_weights[b])) fail(QSV_EINVAL, "non-finite dE weight");
-    const Plan& fwd = get_plan(s, c, false, true);
-    const Plan& adj = get_plan(s, c, true, true);
+    const Plan& fwd = get_plan(s, c, false, true, batch);
+    const Plan& adj = get_plan(s, c, true, true, batch);
     const bool kept = !s->fwd_token.empty() && s->fwd_token == forward_token(s, c, h, params, batch, n_params);
     std::vector<cplx> cf(kept ? 0 : (size_t)batch * fwd.ctab_size), ca((size_t)batch * adj.ctab_size);
     for (size_t b = 0; b < batch; ++b) {
@@ -1055,10 +1061,10 @@ int qsv_expectation_general(qsv_state* psi, const qsv_circuit* c_r, const double
     s->ws_lam.reserve(pair);
     s->ws_aux1.reserve(pair);
     s->ws_aux2.reserve(pair);
-    const Plan& fr = get_plan(s, c_r, false, true);
-    const Plan* ar = grad_r ? &get_plan(s, c_r, true, true) : nullptr;
-    const Plan* fl = c_l ? &get_plan(s, c_l, false, true) : nullptr;
-    const Plan* al = (c_l && grad_l) ? &get_plan(s, c_l, true, true) : nullptr;
+    const Plan& fr = get_plan(s, c_r, false, true, 2);
+    const Plan* ar = grad_r ? &get_plan(s, c_r, true, true, 2) : nullptr;
+    const Plan* fl = c_l ? &get_plan(s, c_l, false, true, 2) : nullptr;
+    const Plan* al = (c_l && grad_l) ? &get_plan(s, c_l, true, true, 2) : nullptr;
     auto bind2 = [&](const Plan* p, const qsv_circuit* c, const double* prm) {
       std::vector<cplx> t(p ? 2 * (size_t)p->ctab_size : 0);
       if (p) {
@@ -1148,8 +1154,8 @@ int qsv_expectation_and_grad_multi(qsv_state* s, const qsv_circuit* c, const qsv
     const size_t one = N * s->amp_bytes();
     s->ws_psi.reserve(n_hams * one);
     s->ws_lam.reserve(n_hams * one);
-    const Plan& fwd = get_plan(s, c, false, true);
-    const Plan& adj = get_plan(s, c, true, true);
+    const Plan& fwd = get_plan(s, c, false, true, 1);
+    const Plan& adj = get_plan(s, c, true, true, n_hams);
     std::vector<cplx> tf(fwd.ctab_size), ta((size_t)n_hams * adj.ctab_size);
     bind_ctab(fwd, c, params, nullptr, 0, tf.data());
     for (size_t k = 0; k < n_hams; ++k) bind_ctab(adj, c, params, nullptr, 0, ta.data() + k * adj.ctab_size);
@@ -1212,11 +1218,11 @@ int qsv_param_shift_grad_batch(qsv_state* s, const qsv_circuit* c, const qsv_pau
         occ.push_back({(int)i, a, g.param_index[a], g.param_coeff[a]});
       }
     }
-    const Plan& fwd = get_plan(s, c, false, false);
     const size_t per = 1 + 2 * occ.size();  // unshifted + shifted variants
     const size_t state_bytes = s->namps() * s->amp_bytes();
     const size_t budget = std::max<size_t>((size_t)8 << 30, s->ws_psi.bytes);
     size_t chunk = std::max<size_t>(1, std::min<size_t>(budget / state_bytes, 4096));
+    const Plan& fwd = get_plan(s, c, false, false, std::min(chunk, per));
     std::vector<double> energies(per);
     for (size_t b = 0; b < batch; ++b) {
       const double* pb = params + b * n_params;

@@ -105,6 +105,33 @@ __device__ __forceinline__ void apply2split(C r0, C r1, C p, C& a0, C& a1) {
   a1.x = fma_s(r1.y, a1.x, p1r);
   a1.y = fma_s(r1.y, a1.y, p1i);
 }
+__host__ __device__ __forceinline__ uint32_t high_word(double v) {
+  uint64_t u;
+  __builtin_memcpy(&u, &v, 8);
+  return (uint32_t)(u >> 32);
+}
+__host__ __device__ __forceinline__ uint32_t high_word(float v) {
+  uint32_t u;
+  __builtin_memcpy(&u, &v, 4);
+  return u;
+}
+// A gate of a phase chain whose matrices keep unit entries (chain_gate): a1 <- a1 p with p = 1 +
+// i t (IMAG: t + i), then (a0, a1) <- (a0 + r0 a1, r1 a0 + a1) (CROSS: (r0 a0 + a1, a0 + r1
+// a1)): one multiply-add per entry that is not 1, 6 instructions per pair, against 12 with a
+// phase and a full real matrix and 16 for the general product.  30-qubit brick in complex128,
+// whole step 210 -> 197 ms (the passes then waited on their waves' latency more than on the
+// vector ALU, see rb_body's SPLIT).
+template <bool IMAG, bool CROSS, typename R, typename C>
+__device__ __forceinline__ void apply2unit(R r0, R r1, R t, C& a0, C& a1) {
+  R x = IMAG ? fmaT(t, a1.x, -a1.y) : fmaT(-t, a1.y, a1.x);
+  R y = IMAG ? fmaT(t, a1.y, a1.x) : fmaT(t, a1.x, a1.y);
+  order(x, y);
+  a1.x = CROSS ? fma_s(r1, x, a0.x) : fma_s(r1, a0.x, x);
+  a1.y = CROSS ? fma_s(r1, y, a0.y) : fma_s(r1, a0.y, y);
+  order(a1.x, a1.y, x, y);  // a0 is overwritten after its last use
+  a0.x = CROSS ? fma_s(r0, a0.x, x) : fma_s(r0, x, a0.x);
+  a0.y = CROSS ? fma_s(r0, a0.y, y) : fma_s(r0, y, a0.y);
+}
 // Matrix forms of one-qubit gates (bits 5-6 of TileOp::plain): general, split (a phase then
 // a real matrix), real (RY, H, X), and real diagonal with imaginary off-diagonal (RX, Y).
 enum MatForm : int { FORM_GENERAL = 0, FORM_SPLIT = 1, FORM_REAL = 2, FORM_XLIKE = 3 };

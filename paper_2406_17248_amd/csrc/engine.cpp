@@ -187,7 +187,36 @@ void dagger_numbers(int type, cplx* v, int count) {
   }
 }
 
-int prim_numbers(const Prim& p, const qsv_circuit* c, const double* ang, cplx* out) {
+// ang: the bound angles of every gate, three each.
+int prim_numbers(const Prim& p, const std::vector<Prim>& parts, const qsv_circuit* c, const double* angles, cplx* out) {
+  if (p.recipe == M_FUSED) {
+    cplx m[4] = {1.0, 0.0, 0.0, 1.0};
+    for (int i = 0; i < p.part_count; ++i) {
+      const Prim& f = parts[p.part_first + i];
+      cplx u[4];
+      if (f.type == P_SIGN) {
+        u[0] = 1.0;
+        u[1] = -1.0;
+      } else {
+        prim_numbers(f, parts, c, angles, u);
+      }
+      if (f.type == P_DENSE1) {
+        const cplx t[4] = {u[0] * m[0] + u[1] * m[2], u[0] * m[1] + u[1] * m[3], u[2] * m[0] + u[3] * m[2],
+                           u[2] * m[1] + u[3] * m[3]};
+        for (int k = 0; k < 4; ++k) m[k] = t[k];
+      } else {
+        for (int k = 0; k < 4; ++k) m[k] *= u[k >> 1];
+      }
+    }
+    if (p.type == P_DENSE1) {
+      for (int k = 0; k < 4; ++k) out[k] = m[k];
+      return 4;
+    }
+    out[0] = m[0];
+    out[1] = m[3];
+    return 2;
+  }
+  const double* ang = angles + 3 * p.gate;
   int cnt = 0;
   const double a = ang[p.angle_slot];
   switch (p.recipe) {
@@ -274,7 +303,7 @@ int32_t default_tile_qubits(int32_t dtype) { return dtype == QSV_C64 ? 12 : 11; 
 int32_t default_adj_tile_qubits(int32_t dtype) { return dtype == QSV_C64 ? 10 : 11; }
 
 PlanOptions state_plan_options(int32_t dtype, int32_t n, int32_t tile, int32_t adj_tile, bool adjoint, bool fuse_zz,
-                               bool relayout) {
+                               bool relayout, size_t batch) {
   PlanOptions o;
   o.relayout = relayout && !adjoint;
   o.tile_qubits = adjoint ? adj_tile : tile;
@@ -304,9 +333,15 @@ PlanOptions state_plan_options(int32_t dtype, int32_t n, int32_t tile, int32_t a
   // vector ALU's other work; 4.5 is the best of 3.5 / 4.5 / 5.5 / none (brick: -7 %).
   o.blocks = !adjoint && dtype == QSV_C64;
   o.block_min_gates = 3.0;
-  // complex128 forward passes split one-qubit gates instead: a phase and a real 2x2 matrix
-  // cost 12 vector instructions per amplitude pair instead of 16, more than a block saves
-  o.split = !adjoint && dtype == QSV_C128;
+  // complex128 forward passes fuse a qubit's one-qubit gates and split them: a phase and a real
+  // 2x2 matrix with unit entries cost 6 vector instructions per amplitude pair instead of 16.
+  // (complex64 ones ran 22 % faster than with the blocks on the 27-qubit brick, with the same
+  // error in the amplitudes, but energies came out 1.4 times further off: fewer gate matrices
+  // are rounded to 32 bits in the blocks.)
+  o.split = o.fuse1 = !adjoint && dtype == QSV_C128;
+  // (rb_body's SPLIT: more resident waves pay once there are more workgroups than fit)
+  const int m = std::min<int>(std::max(o.tile_qubits, 2), n);
+  o.half_remap = !adjoint && (batch << (n - m)) > kWarmTiles;
   return o;
 }
 
@@ -467,6 +502,68 @@ std::vector<Prim> lower_adjoint(const qsv_circuit* c) {
       p.coeff = g.param_coeff[0];
     }
     out.push_back(p);
+  }
+  return out;
+}
+
+// One-qubit primitives of one qubit with nothing but diagonal primitives on it between them, as
+// one primitive: a phase (or Z) joins the one-qubit gate before it, or the next one after it;
+// a gate joins the one right before it.  Everything else keeps its order.
+static std::vector<Prim> fuse_one_qubit(const std::vector<Prim>& in, int n, std::vector<Prim>& parts) {
+  std::vector<Prim> out;
+  std::vector<std::vector<Prim>> own;               // parts of out's one-qubit primitives
+  std::vector<int> gate(n, -1), tail(n, -1);        // last gate of q since which q saw only
+                                                    // diagonal primitives; ... saw nothing
+  std::vector<std::vector<Prim>> held(n);           // phases of q that wait for its next gate
+  auto append = [&](const Prim& p, std::vector<Prim> f) {
+    out.push_back(p);
+    own.push_back(std::move(f));
+  };
+  auto release = [&](int q) {  // the waiting phases by themselves
+    if (held[q].empty()) return;
+    Prim d = held[q][0];
+    if (held[q].size() > 1) {
+      d.type = P_DIAG1;
+      d.cmask = 0;
+      d.touched = 1ull << q;
+    }
+    append(d, std::move(held[q]));
+    held[q].clear();
+  };
+  for (const Prim& p : in) {
+    const bool one = (p.type == P_DENSE1 || p.type == P_DIAG1) && p.cmask == 0;
+    const bool z = p.type == P_SIGN && popc(p.cmask) == 1;
+    const int q = z ? __builtin_ctzll(p.cmask) : p.q0;
+    if (one && p.type == P_DENSE1) {
+      if (tail[q] >= 0) {
+        own[tail[q]].push_back(p);
+        continue;
+      }
+      std::vector<Prim> f = std::move(held[q]);
+      held[q].clear();
+      f.push_back(p);
+      gate[q] = tail[q] = (int)out.size();
+      append(p, std::move(f));
+    } else if (one || z) {
+      if (gate[q] >= 0) own[gate[q]].push_back(p);
+      else held[q].push_back(p);
+    } else {
+      for (uint64_t t = p.touched; t; t &= t - 1) tail[__builtin_ctzll(t)] = -1;
+      for (uint64_t t = p.nondiag; t; t &= t - 1) {
+        release(__builtin_ctzll(t));
+        gate[__builtin_ctzll(t)] = -1;
+      }
+      append(p, {});
+    }
+  }
+  for (int q = 0; q < n; ++q) release(q);
+  for (size_t i = 0; i < out.size(); ++i) {
+    if (own[i].size() < 2) continue;
+    Prim& p = out[i];
+    p.recipe = M_FUSED;
+    p.part_first = (int32_t)parts.size();
+    p.part_count = (int32_t)own[i].size();
+    parts.insert(parts.end(), own[i].begin(), own[i].end());
   }
   return out;
 }
@@ -766,6 +863,17 @@ struct PassEmitter {
     plan.ops.push_back(op);
     op_param.push_back(param);
   }
+  int row_bits = 4;  // of the pass's LDS exchange (lds_swizzle)
+  uint64_t lds_units(const RbLayout& L) const {
+    uint64_t u = 0;
+    for (int i = 0; i < L.r; ++i) u |= (uint64_t)lds_swizzle(1 << L.reg[i], row_bits) << (16 * i);
+    return u;
+  }
+  void set_units(TileOp& op, const RbLayout& L) const {
+    const uint64_t u = lds_units(L);
+    op.pslot = (int32_t)(uint32_t)u;
+    op.gkind = (int32_t)(uint32_t)(u >> 32);
+  }
   // Move to layout L through LDS.
   void remap(const RbLayout& L) {
     TileOp op{};
@@ -774,7 +882,7 @@ struct PassEmitter {
     op.b = (int32_t)L.regpack();
     op.omask = L.thrpack();
     op.gen = -1;
-    op.pslot = -1;
+    set_units(op, L);
     push(op, -1);
     lay = L;
   }
@@ -792,7 +900,7 @@ struct PassEmitter {
       op.b = (int32_t)lay.regpack();
       op.omask = lay.thrpack();
       op.gen = -1;
-      op.pslot = -1;
+      set_units(op, lay);
       push(op, -1);
     }
   }
@@ -1066,6 +1174,7 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
   plan.n_qubits = c->n_qubits;
   plan.prims = adjoint ? lower_adjoint(c) : lower_forward(c);
   const int n = c->n_qubits;
+  if (!adjoint && opt.fuse1 && opt.tile_qubits != 0) plan.prims = fuse_one_qubit(plan.prims, n, plan.parts);
   auto alloc = [&](int count) {
     const int off = plan.ctab_size;
     plan.ctab_size += count;
@@ -1152,30 +1261,40 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
   // dense.
   std::vector<char> chain(plan.prims.size(), 0);
   if (rb && opt.split && !adjoint && !opt.blocks) {
-    // (gates with real or X-like matrices cost 8 instructions per pair as they are, fewer
-    // than a split gate's 12, so they neither join nor extend chains)
+    auto unitary = [&](const Prim& pr) {
+      return pr.recipe != M_GATE || c->gates[pr.gate].kind != QSV_GATE_MAT1 || mat1_is_unitary(c, c->gates[pr.gate]);
+    };
     auto splittable = [&](int32_t i) {
       const Prim& pr = plan.prims[i];
-      if (pr.type != P_DENSE1 || pr.cmask != 0 || matrix_form(pr, c) != 0) return false;
-      const qsv_gate& g = c->gates[pr.gate];
-      return pr.recipe != M_GATE || g.kind != QSV_GATE_MAT1 || mat1_is_unitary(c, g);
+      if (pr.type != P_DENSE1 || pr.cmask != 0) return false;
+      if (pr.recipe == M_GATE && c->gates[pr.gate].kind == QSV_GATE_X) return false;  // a swap
+      if (pr.recipe != M_FUSED) return unitary(pr);
+      for (int k = 0; k < pr.part_count; ++k)
+        if (!unitary(plan.parts[pr.part_first + k])) return false;
+      return true;
     };
-    std::vector<int32_t> last(n, -1);  // each qubit's previous non-diagonal primitive
+    // Vector instructions per amplitude pair: a chain's gates take 6 each and its last one 16;
+    // by themselves gates with real or X-like matrices take 8, others 16.
+    std::vector<std::vector<int32_t>> run(n);  // each qubit's gates in a row that can join
+    auto close = [&](int q) {
+      const std::vector<int32_t>& r = run[q];
+      int alone = 0;
+      for (int32_t i : r) alone += matrix_form(plan.prims[i], c) != 0 ? 8 : 16;
+      if (r.size() >= 2 && 6 * ((int)r.size() - 1) + 16 < alone) {
+        for (int32_t i : r) chain[i] = 1;
+        chain[r.back()] = 2;
+      }
+      run[q].clear();
+    };
     for (int pi = 0; pi < P; ++pi)
       for (const Pass& rd : pass_rounds[pi])
-        for (int32_t i : rd.prims) {
-          uint64_t nd = plan.prims[i].nondiag;
-          while (nd) {
+        for (int32_t i : rd.prims)
+          for (uint64_t nd = plan.prims[i].nondiag; nd; nd &= nd - 1) {
             const int q = __builtin_ctzll(nd);
-            nd &= nd - 1;
-            const int32_t prev = last[q];
-            if (prev >= 0 && splittable(prev) && splittable(i)) {
-              chain[prev] = 1;
-              if (!chain[i]) chain[i] = 2;
-            }
-            last[q] = i;
+            if (splittable(i)) run[q].push_back(i);
+            else close(q);
           }
-        }
+    for (int q = 0; q < n; ++q) close(q);
   }
   for (int pi = 0; pi < P; ++pi) {
     const Pass& ps = passes[pi];
@@ -1190,6 +1309,12 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
     dp.edge_lo = (int32_t)plan.edges.size();
     dp.pslot_first = plan.n_pslots;
     PassEmitter em{plan, c, adjoint, opt, ps.tile_mask, {}, {}};
+    if (rb && opt.half_remap && !adjoint) {
+      dp.half_remap = 1;
+      for (int32_t i : ps.prims)
+        if (plan.prims[i].type == P_DENSE2) dp.half_remap = 0;
+    }
+    em.row_bits = (opt.dtype == QSV_C64 ? 4 : 3) + (dp.half_remap ? 1 : 0);
     {
       int r = 0;
       for (int q = 0; q < 64; ++q) em.loc[q] = (ps.tile_mask >> q & 1) ? r++ : -1;
@@ -1459,6 +1584,8 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
       plan.n_pslots += dp.pslot_count;
     }
     dp.op_count = (int32_t)plan.ops.size() - dp.op_first;
+    for (int i = 0; rb && i < reg_bits; ++i)
+      dp.lay0_units |= (uint64_t)lds_swizzle(1 << ((dp.lay0_reg >> (8 * i)) & 255), em.row_bits) << (16 * i);
     dp.ctab_n = plan.ctab_size - dp.ctab_lo;
     dp.diag_n = (int32_t)plan.diag.size() - dp.diag_lo;
     dp.edge_n = (int32_t)plan.edges.size() - dp.edge_lo;
@@ -1543,8 +1670,9 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
 std::string structure_key(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
   std::string key;
   auto put = [&](const void* p, size_t n) { key.append(reinterpret_cast<const char*>(p), n); };
-  const int32_t head[10] = {c->n_qubits, adjoint ? 1 : 0, opt.tile_qubits, opt.low_qubits, opt.fuse_zz ? 1 : 0,
-                            opt.dtype, opt.use_rb ? 1 : 0, opt.rb_min, opt.reg_bits, opt.relayout ? 1 : 0};
+  const int32_t head[14] = {c->n_qubits, adjoint ? 1 : 0, opt.tile_qubits, opt.low_qubits, opt.fuse_zz ? 1 : 0,
+                            opt.dtype, opt.use_rb ? 1 : 0, opt.rb_min, opt.reg_bits, opt.relayout ? 1 : 0,
+                            opt.blocks ? 1 : 0, opt.split ? 1 : 0, opt.fuse1 ? 1 : 0, opt.half_remap ? 1 : 0};
   put(head, sizeof(head));
   for (size_t i = 0; i < c->n_gates; ++i) {
     const qsv_gate& g = c->gates[i];
@@ -1604,7 +1732,7 @@ static void block_matrix(const Plan& p, const qsv_circuit* c, const std::vector<
   for (int32_t pi : b.prims) {
     const Prim& pr = p.prims[pi];
     cplx num[16];
-    prim_numbers(pr, c, &ang[3 * pr.gate], num);
+    prim_numbers(pr, p.parts, c, ang.data(), num);
     if (pr.type == P_DENSE1) {
       const int t = bit_of(pr.q0);
       for (int col = 0; col < 8; ++col)
@@ -1662,12 +1790,53 @@ void split_gate(const cplx* M, cplx* left, cplx* out) {
   out[2] = ph;
 }
 
+void chain_gate(const cplx* M, bool normalize, cplx* carry, cplx* out) {
+  const cplx k[2] = {carry[0], carry[1]};
+  const double k0 = std::abs(k[0]), rho = std::abs(k[1]) / k0;
+  cplx U[4], left[2];
+  for (int r = 0; r < 2; ++r) {
+    U[2 * r] = M[2 * r] * (k[0] / k0);
+    U[2 * r + 1] = M[2 * r + 1] * (k[1] / (k0 * rho));
+  }
+  split_gate(U, left, out);
+  const double cs = out[0].real(), sn = out[1].real();
+  const cplx ph = out[2];
+  if (normalize) {
+    out[0] = cplx(k0 * cs, -k0 * sn * rho);
+    out[1] = cplx(k0 * sn, k0 * cs * rho);
+    out[3] = (double)kChainFull;
+    carry[0] = left[0];
+    carry[1] = left[1];
+  } else {
+    // p keeps the larger of its two parts at 1; g: what is left for R's second column
+    const bool imag = std::abs(ph.imag()) > std::abs(ph.real());
+    const double g = rho * (imag ? ph.imag() : ph.real());
+    out[2] = imag ? cplx(ph.real() / ph.imag(), 1.0) : cplx(1.0, ph.imag() / ph.real());
+    // [[c, -s g], [s, c g]] with its larger entries at 1
+    const bool cross = sn > cs;
+    if (cross) {
+      out[0] = cplx(-cs / (sn * g), 1.0);
+      out[1] = cplx(1.0, cs * g / sn);
+      carry[0] = k0 * left[0] * (-sn * g);
+      carry[1] = k0 * left[1] * sn;
+    } else {
+      out[0] = cplx(1.0, -sn * g / cs);
+      out[1] = cplx(sn / (cs * g), 1.0);
+      carry[0] = k0 * left[0] * cs;
+      carry[1] = k0 * left[1] * (cs * g);
+    }
+    out[3] = (double)(kChainUnit + (imag ? kChainImag : 0) + (cross ? kChainCross : 0));
+  }
+}
+
 void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const AngleOverride* ov, int n_ov,
                cplx* out) {
   std::vector<double> ang(3 * c->n_gates);
   for (size_t i = 0; i < c->n_gates; ++i) gate_angles(c->gates[i], params, &ang[3 * i]);
   for (int k = 0; k < n_ov; ++k) ang[3 * ov[k].gate + ov[k].slot] = ov[k].angle;
-  // phase chains: the left diagonal each qubit carries to its next gate
+  // phase chains: the left diagonal each qubit carries to its next gate, and its gates since the
+  // diagonal's moduli were last folded in
+  std::vector<int> gates_since((size_t)c->n_qubits, 0);
   std::vector<cplx> carry(2 * (size_t)c->n_qubits, cplx(1.0, 0.0));
   for (const Fill& f : p.fills) {
     cplx* dst = out + f.offset;
@@ -1675,24 +1844,23 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
       case F_GATE_CHAIN: {
         const Prim& pr = p.prims[f.prim];
         cplx M[4];
-        prim_numbers(pr, c, &ang[3 * pr.gate], M);
+        prim_numbers(pr, p.parts, c, ang.data(), M);
         cplx* cq = &carry[2 * (size_t)pr.q0];
-        for (int r = 0; r < 2; ++r) {
-          M[2 * r] *= cq[0];
-          M[2 * r + 1] *= cq[1];
-        }
+        int& since = gates_since[pr.q0];
         if (f.count) {
-          split_gate(M, cq, dst);
-          dst[3] = 0.0;
+          const bool normalize = since >= kChainGates;
+          chain_gate(M, normalize, cq, dst);
+          since = normalize ? 0 : since + 1;
         } else {
-          for (int e = 0; e < 4; ++e) dst[e] = M[e];
+          for (int e = 0; e < 4; ++e) dst[e] = M[e] * cq[e & 1];
           cq[0] = cq[1] = cplx(1.0, 0.0);
+          since = 0;
         }
         break;
       }
       case F_PRIM_MATRIX: {
         const Prim& pr = p.prims[f.prim];
-        prim_numbers(pr, c, &ang[3 * pr.gate], dst);
+        prim_numbers(pr, p.parts, c, ang.data(), dst);
         break;
       }
       case F_PRIM_GEN:

@@ -36,6 +36,8 @@ enum MatRecipe : int32_t {
   M_RX_PLUS,     // RX(+pi/2) (basis change of a lowered RYY)
   M_RX_MINUS,    // RX(-pi/2)
   M_ZZ_ANGLE,    // diag(e^{-i a/2}, e^{i a/2}, e^{i a/2}, e^{-i a/2}), a = angle[0]
+  M_FUSED,       // the product of one-qubit primitives of one qubit: Plan::parts
+                 // [part_first, part_first + part_count), in execution order
 };
 
 enum PrimType : int32_t { P_DENSE1 = 0, P_DENSE2, P_DIAG1, P_DIAG2, P_SIGN };
@@ -54,6 +56,7 @@ struct Prim {
   // planning masks
   uint64_t nondiag;     // qubits acted on non-diagonally (must be tile qubits)
   uint64_t touched;     // every qubit involved (targets and controls)
+  int32_t  part_first = 0, part_count = 0;  // M_FUSED
 };
 
 struct Pass {
@@ -70,10 +73,11 @@ enum FillKind : int32_t {
   F_ZZ_GEN,           // coeff * (E - 2c) as real weights
   F_BLOCK,            // the product of a fused block's primitives as matrix-core operands
                       // (Fill::prim indexes Plan::blocks; 128 entries)
-  F_GATE_CHAIN,       // a one-qubit gate of a phase chain (Plan::split): its matrix times the
-                      // phase its qubit carries from the previous gate of the chain; count = 1:
-                      // split into (real matrix, phase), the left phase carried on, count = 0:
-                      // the chain's last gate, dense (4 entries either way)
+  F_GATE_CHAIN,       // a one-qubit gate of a phase chain (PlanOptions::split): its matrix
+                      // times the diagonal that its qubit carries from the previous gate of the
+                      // chain; count = 1: split into (real matrix, phase) by chain_gate, the
+                      // left diagonal carried on, count = 0: the chain's last gate, dense (4
+                      // entries either way)
 };
 struct Fill {
   int32_t kind;
@@ -139,6 +143,8 @@ struct DevPass {
   int32_t  dep_first;      // register-blocked: first of the pass's kDepEntries Plan::deps entries
   int32_t  relayout;       // register-blocked: stores go to another layout (and buffer)
   int32_t  ctab_lo, ctab_n, diag_lo, diag_n, edge_lo, edge_n;  // the pass's parts of the tables
+  int32_t  half_remap;     // register-blocked: remaps in two halves (see PassArgs)
+  uint64_t lay0_units;
 };
 
 // Launches of at most this many tiles read the pass's tables into L2 ahead of use (four
@@ -152,6 +158,8 @@ inline void set_table_parts(PassArgs& A, const DevPass& dp, int32_t warm) {
   A.edge_lo = dp.edge_lo;
   A.edge_n = dp.edge_n;
   A.warm = warm;
+  A.half_remap = dp.half_remap;
+  A.lay0_units = dp.lay0_units;
 }
 
 // A fully planned execution (forward or adjoint reverse sweep) of one circuit structure.
@@ -168,6 +176,7 @@ struct Plan {
   bool unfused = false;     // per-primitive streaming kernels
   int32_t n_qubits = 0;
   std::vector<Prim> prims;
+  std::vector<Prim> parts;  // of M_FUSED primitives
   std::vector<DevPass> passes;
   // register-blocked passes, kDepEntries per pass (layout in qsv_ops.h): where each local
   // index is read and written, and runs forming a tile's logical, load and store bases
@@ -205,6 +214,10 @@ struct PlanOptions {
                               // one-qubit gates followed on their qubit by another such gate
                               // run as a phase and a real 2x2 matrix; the rest of the gate (a
                               // diagonal) is carried into the qubit's next gate
+  bool    half_remap = false; // complex128 forward register-blocked passes without two-qubit
+                              // matrices remap in two halves, through half the LDS
+  bool    fuse1 = false;      // forward plans: one-qubit gates and phases of one qubit with
+                              // nothing but diagonal gates between them run as one gate
 };
 
 // Block index bit b of an 8x8 fused block and the real 16x16 matrix-core operands: the real
@@ -219,6 +232,17 @@ void block_operands(const cplx* M8, int dtype, double* out);
 // (R00, R01) and out[1] = (R10, R11) as complex pairs of reals.
 void split_gate(const cplx* M, cplx* left, cplx* out);
 
+// A gate of a phase chain: unitary M (row-major) after the diagonal `carry` that its qubit
+// brings along equals diag(new carry) R diag(1, p); out[0] = (R00, R01) and out[1] = (R10,
+// R11) as complex pairs of reals, out[2] = p, out[3].x the form (kChain*).  R keeps two unit
+// entries and p a unit real or imaginary part (its modulus and R's are carried), so that
+// kernels spend one multiply-add on each of the others; the carried moduli shrink by up to a
+// half per gate.  normalize: R with its moduli, p a phase, and the new carry of modulus 1.
+void chain_gate(const cplx* M, bool normalize, cplx* carry, cplx* out);
+// Gates between normalizing ones, so that unnormalized amplitudes (up to 2^gates larger per
+// qubit, 34 qubits) stay finite in double: 2^(15 * 34) < 2^1023.
+constexpr int kChainGates = 15;
+
 // Default tile widths of forward and adjoint plans, measured on the 30-qubit brick circuit
 // (forward) and the 24-qubit QAOA batch (adjoint): wider tiles save passes but need more
 // REMAPs per pass.
@@ -227,7 +251,7 @@ int32_t default_adj_tile_qubits(int32_t dtype);
 // Plan options of a state's forward or adjoint plan, from its dtype, qubit count and tile
 // width options (the one place these rules live, used by the library and the host checks).
 PlanOptions state_plan_options(int32_t dtype, int32_t n, int32_t tile, int32_t adj_tile, bool adjoint, bool fuse_zz,
-                               bool relayout);
+                               bool relayout, size_t batch = 1);
 
 // Validate a circuit against n_params (and the state's n).  Throws Error.
 void validate_circuit(const qsv_circuit* c, size_t n_params, int32_t n_state);

@@ -21,7 +21,8 @@ enum OpType : int32_t {
                   // two bits) has byte i of (a, b, lmask) edges
   OP_REMAP = 4,   // register-blocked passes: move amplitudes through LDS into a new
                   // layout: register (slot) bit i holds local bit (b >> 8i) & 255, thread
-                  // bit t holds local bit (omask >> 4t) & 15; `a` is the register mask
+                  // bit t holds local bit (omask >> 4t) & 15; `a` is the register mask;
+                  // (gkind, pslot) the LDS address terms of its register bits (lds_units)
   OP_XSWAP = 5,   // register-blocked passes: one transposition, `mat` = slot bit (low 2
                   // bits) | lane bit (4 or 5) << 4, exchanging the local bit on a register
                   // slot bit with the one on lane bit 4 or 5 of the wave by cross-lane moves
@@ -37,6 +38,15 @@ enum OpType : int32_t {
                   // partner satisfy the controls on slots) (| kPlainOutside: omask is not 0);
                   // first = the controls on thread bits, in j-space
 };
+// LDS position of local index j: the low bits of j (3 for 16-byte elements, 4 for 8-byte ones:
+// the elements of a 128-byte row) XORed with the higher ones, so that every layout spreads over
+// the banks.  Linear over GF(2): a register block's slots are a per-thread term XOR the terms
+// of the register bits set in the slot number, 16 bits each in lds_units.
+constexpr int lds_swizzle(int j, int row_bits) {
+  int f = 0;
+  for (int sh = row_bits; sh < 16; sh += row_bits) f ^= j >> sh;
+  return j ^ (f & ((1 << row_bits) - 1));
+}
 // In register-blocked passes each thread holds 2^RB amplitudes; DENSE1 then names a
 // register-bit index (a in [0, RB)) instead of a local bit, and the other ops are
 // elementwise.  A DENSE1 op with b = 1 first applies the sign-only diagonal run
@@ -55,7 +65,7 @@ struct TileOp {
   // (kPlainSigns), has plain = 1 + slot (| kPlainSigns)
   // | the form of its matrix (kPlainForm bits): kPlainSplit, a phase on the slot's 1 half
   // then a real 2x2 matrix (ctab[mat] = (R00, R01), ctab[mat + 1] = (R10, R11), ctab[mat + 2]
-  // = the phase); kPlainReal, a real matrix (RY, H, X); kPlainXlike, real diagonal and
+  // = the phase, ctab[mat + 3].x = which of their entries are 1, kChain*); kPlainReal, a real matrix (RY, H, X); kPlainXlike, real diagonal and
   // imaginary off-diagonal entries (RX, Y); none: a general 2x2.  A fused block has plain =
   // kPlainBlock | (1 + slot) (| kPlainSigns).  The kernel reads the first eight fields at once
   // and decodes nothing else for these ops.  0 for every other op.
@@ -79,6 +89,9 @@ constexpr int32_t kPlainSplit = 32, kPlainReal = 64, kPlainXlike = 96, kPlainFor
 constexpr int32_t kPlainFlip = 128, kPlainOutside = 256;
 static_assert(offsetof(TileOp, plain) == 0 && offsetof(TileOp, gkind) == 28 && alignof(TileOp) == 8,
               "plain .. gkind form the record's first 32 bytes");
+// Forms of split gates (see chain_gate): 0, any R and a phase p; else 1 + (p.y = 1 instead of
+// p.x = 1) + 2 (R01 = R10 = 1 instead of R00 = R11 = 1).
+enum ChainForm : int32_t { kChainFull = 0, kChainUnit = 1, kChainImag = 1, kChainCross = 2 };
 // Generator forms of DENSE1 ops (k = the chain-rule factor, read from the generator table):
 // GEN_GENERAL: any 2x2; GEN_X: k X (ctab[gen + 1] = k); GEN_Y: k Y (ctab[gen + 2] = i k).
 enum GenForm : int32_t { GEN_GENERAL = 0, GEN_X = 1, GEN_Y = 2 };
@@ -176,6 +189,9 @@ struct PassArgs {
   // [diag_lo, diag_lo + diag_n) and edges [edge_lo, edge_lo + edge_n)
   int32_t      ctab_lo, ctab_n, diag_lo, diag_n, edge_lo, edge_n;
   int32_t      warm;          // 1: read these ahead of their use
+  int32_t      half_remap;    // 1: remaps move real and imaginary parts separately (the LDS
+                              // terms below and in OP_REMAP are for 8-byte elements)
+  uint64_t     lay0_units;    // load layout: LDS address terms of its register bits
 };
 
 // Adjoint register-blocked passes keep each gradient slot's per-wave sums in LDS until the

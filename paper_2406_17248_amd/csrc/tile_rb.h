@@ -2,6 +2,7 @@
 // direction at a time by tile_rb.hip.
 #pragma once
 #include <algorithm>
+#include <type_traits>
 
 #include "device_util.h"
 #include "qsv_kernels.h"
@@ -16,13 +17,8 @@ namespace qsv {
 // every access pattern spreads over the banks).  Gates on other bits are never issued:
 // the planner groups each pass's gates into register rounds.
 // ------------------------------------------------------------------------------------------
-template <int S>  // S = log2(amplitudes per 128-byte LDS row)
-__device__ __forceinline__ int swz(int j) {
-  int f = 0;
-#pragma unroll
-  for (int sh = S; sh < 16; sh += S) f ^= j >> sh;
-  return j ^ (f & ((1 << S) - 1));
-}
+template <int S>  // S = log2(elements per 128-byte LDS row)
+__device__ __forceinline__ int swz(int j) { return lds_swizzle(j, S); }
 
 // dst <- src in the lanes set in the wave-uniform lane mask, written in place (a select
 // whose result the compiler could put in a new register would make it carry the register
@@ -203,11 +199,23 @@ template <int I, int NR, bool ADJ, int GK, typename C, int F = FORM_GENERAL>
 __device__ __forceinline__ void reg1(C* v, C* w, int jt, uint32_t reg, uint32_t lm, const C* U, bool grad,
                                      const C* G, double& acc) {
   if constexpr (F == FORM_SPLIT) {  // forward, uncontrolled
+    const auto each = [&](auto f) {
 #pragma unroll
-    for (int k = 0; k < NR; ++k) {
-      if (k & (1 << I)) continue;
-      apply2split(U[0], U[1], U[2], v[k], v[k | (1 << I)]);
-    }
+      for (int k = 0; k < NR; ++k)
+        if (!(k & (1 << I))) f(v[k], v[k | (1 << I)]);
+    };
+    const uint32_t form = high_word(U[3].x);  // wave-uniform
+    using R = decltype(U[0].x);
+    if (form == high_word((R)kChainUnit))
+      each([&](C& a, C& b) { apply2unit<false, false>(U[0].y, U[1].x, U[2].y, a, b); });
+    else if (form == high_word((R)(kChainUnit + kChainImag)))
+      each([&](C& a, C& b) { apply2unit<true, false>(U[0].y, U[1].x, U[2].x, a, b); });
+    else if (form == high_word((R)(kChainUnit + kChainCross)))
+      each([&](C& a, C& b) { apply2unit<false, true>(U[0].x, U[1].y, U[2].y, a, b); });
+    else if (form == high_word((R)(kChainUnit + kChainImag + kChainCross)))
+      each([&](C& a, C& b) { apply2unit<true, true>(U[0].x, U[1].y, U[2].x, a, b); });
+    else
+      each([&](C& a, C& b) { apply2split(U[0], U[1], U[2], a, b); });
     return;
   }
   if (lm == 0) {
@@ -419,14 +427,24 @@ __device__ __forceinline__ uint32_t sign_slots(const DiagEntry* d, int count, ui
 }
 
 // FULL: the tile fills the workgroup (m == MAXM), so every thread holds amplitudes.
-template <typename R, int RB, int MAXM, bool ADJ, bool FULL>
+// SPLIT (forward passes without two-qubit matrices, in launches of many tiles): remaps move the
+// real and the imaginary parts one after the other through half the LDS.  A pass waits more
+// than it computes (scalar loads, branches, remaps: with four waves per SIMD the vector ALU
+// was busy 56 % of the time), so it wants resident waves: half the exchange buffer and 72
+// registers allow seven per SIMD where LDS allowed four.  30-qubit brick in complex128, whole
+// step: 197 -> 142 ms (five waves 164, six 149; eight spill); 27 qubits in complex64: 14.8 ->
+// 13.9 ms.  In launches that leave the chip idle the two further barriers only cost (10-qubit
+// ansatz 231 -> 257 us); the reverse sweep's registers do not fit five waves.
+constexpr int kSplitWaves = 7;
+template <typename R, int RB, int MAXM, bool ADJ, bool FULL, bool SPLIT = false>
 __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, const int b) {
   using C = typename CT<R>::T;
   static_assert(RB == 3 || RB == 4, "register blocks of three or four bits");
   constexpr int NT = 1 << (MAXM - RB);
   constexpr int NR = 1 << RB;
-  constexpr int S = sizeof(R) == 8 ? 3 : 4;
-  __shared__ C buf[1 << MAXM];
+  using X = std::conditional_t<SPLIT, R, C>;    // what one exchange moves per amplitude
+  constexpr int S = sizeof(X) == 16 ? 3 : sizeof(X) == 8 ? 4 : 5;
+  __shared__ X buf[1 << MAXM];
   __shared__ double red[NT >= 64 ? NT / 64 : 1];
 
   const int tid = threadIdx.x;
@@ -471,12 +489,12 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
   };
   // LDS byte address of register slot k.  swz is linear over GF(2) and slot k's local index is
   // the thread part (slot 0) with the bits of k spread over the register bits, so the address
-  // is a per-thread term, swz(thread part), XOR a wave-uniform term, swz(spread of k): moving
-  // a register block through LDS costs one XOR per slot.
-  auto slot_offsets = [&](uint32_t reg, int* off) {
+  // is a per-thread term, swz(thread part), XOR a wave-uniform term, swz(spread of k), itself
+  // the XOR of the register bits' terms: 16 bits each of the planner's `units`.
+  auto slot_offsets = [&](uint64_t units, int* off) {
     int u[RB];
 #pragma unroll
-    for (int i = 0; i < RB; ++i) u[i] = swz<S>(1 << (int)((reg >> (8 * i)) & 255)) * (int)sizeof(C);
+    for (int i = 0; i < RB; ++i) u[i] = (int)((units >> (16 * i)) & 0xffff) * (int)sizeof(X);
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       int o = 0;
@@ -486,7 +504,7 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
       off[k] = o;
     }
   };
-  auto lds_at = [&](int byte_off) -> C& { return *reinterpret_cast<C*>(reinterpret_cast<char*>(buf) + byte_off); };
+  auto lds_at = [&](int byte_off) -> X& { return *reinterpret_cast<X*>(reinterpret_cast<char*>(buf) + byte_off); };
   // Tables ahead of use: the ops read their records and numbers one dependent scalar load
   // after another, and right after an upload each of those loads comes from HBM.  One vector
   // load per 128-byte line brings all of them into this XCD's L2 at once, while the tile
@@ -527,7 +545,8 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
 
   int jt = layout(A.lay0_thr);                         // the thread's part of its local indices
   uint32_t reg_cur = A.lay0_reg;                       // register bits of the current layout
-  int sw_cur = swz<S>(jt) * (int)sizeof(C);            // per-thread term of its LDS addresses
+  uint64_t units_cur = A.lay0_units;                   // its register bits' terms of LDS addresses
+  int sw_cur = swz<S>(jt) * (int)sizeof(X);            // per-thread term of its LDS addresses
   auto globals = [&](uint64_t tile_base, uint64_t* xo) {
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
@@ -667,7 +686,8 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
         // the new layout: register slot bits, thread bits, the thread's part of its indices
         const uint32_t lr = (uint32_t)ld(&O->b);
         const int jn = layout(ld(&O->omask));
-        const int sw_new = swz<S>(jn) * (int)sizeof(C);
+        const int sw_new = swz<S>(jn) * (int)sizeof(X);
+        const uint64_t units = (uint64_t)(uint32_t)ld(&O->gkind) << 32 | (uint32_t)ld(&O->pslot);
         if (type == OP_XSWAP) {
           // one transposition per op, by cross-lane moves; every lane takes part (partners
           // of active lanes are active)
@@ -676,33 +696,51 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
           if (ADJ) xswap_dispatch<RB>(code, w);
         } else {
           int uo[NR], un[NR];
-          slot_offsets(reg_cur, uo);
-          slot_offsets(lr, un);
-          if (active) {
+          slot_offsets(units_cur, uo);
+          slot_offsets(units, un);
+          if constexpr (SPLIT) {
+            auto exchange = [&](auto part) {  // part(k): the component that moves
+              if (active) {
 #pragma unroll
-            for (int k = 0; k < NR; ++k) lds_at(sw_cur ^ uo[k]) = v[k];
-          }
-          __syncthreads();
-          if (active) {
+                for (int k = 0; k < NR; ++k) lds_at(sw_cur ^ uo[k]) = part(k);
+              }
+              __syncthreads();
+              if (active) {
 #pragma unroll
-            for (int k = 0; k < NR; ++k) v[k] = lds_at(sw_new ^ un[k]);
-          }
-          if (ADJ) {
-            __syncthreads();
+                for (int k = 0; k < NR; ++k) part(k) = lds_at(sw_new ^ un[k]);
+              }
+              __syncthreads();
+            };
+            exchange([&](int k) -> R& { return v[k].x; });
+            exchange([&](int k) -> R& { return v[k].y; });
+          } else {
             if (active) {
 #pragma unroll
-              for (int k = 0; k < NR; ++k) lds_at(sw_cur ^ uo[k]) = w[k];
+              for (int k = 0; k < NR; ++k) lds_at(sw_cur ^ uo[k]) = v[k];
             }
             __syncthreads();
             if (active) {
 #pragma unroll
-              for (int k = 0; k < NR; ++k) w[k] = lds_at(sw_new ^ un[k]);
+              for (int k = 0; k < NR; ++k) v[k] = lds_at(sw_new ^ un[k]);
             }
+            if (ADJ) {
+              __syncthreads();
+              if (active) {
+#pragma unroll
+                for (int k = 0; k < NR; ++k) lds_at(sw_cur ^ uo[k]) = w[k];
+              }
+              __syncthreads();
+              if (active) {
+#pragma unroll
+                for (int k = 0; k < NR; ++k) w[k] = lds_at(sw_new ^ un[k]);
+              }
+            }
+            __syncthreads();
           }
-          __syncthreads();
         }
         jt = jn;
         reg_cur = lr;
+        units_cur = units;
         sw_cur = sw_new;
       } else if (on && active && type == OP_DENSE1) {
         C U[4], G[4];
@@ -714,14 +752,15 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
           for (int r = 0; r < 4; ++r) G[r] = ldc(T + gen + r);
         }
         reg1_dispatch<RB, ADJ>(ld(&O->a), v, w, jt, reg_cur, lmask, U, grad, ADJ ? gkind : 0, G, acc);
-      } else if (on && type == OP_DENSE2) {
+      } else if (!SPLIT && on && type == OP_DENSE2) {
+       if constexpr (!SPLIT) {
         // two-qubit dense gate on local bits a, b, applied to the tile staged in LDS (no
         // gradient: parameterized two-qubit rotations are lowered to RZZ with basis changes)
         const int a = ld(&O->a), bb = ld(&O->b);
         const int lo = a < bb ? a : bb, hi = a < bb ? bb : a;
         const uint32_t lm = lmask;
         int uo[NR];
-        slot_offsets(reg_cur, uo);
+        slot_offsets(units_cur, uo);
         auto apply_staged = [&](C (&reg)[NR]) {
           if (active) {
 #pragma unroll
@@ -753,6 +792,7 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
         };
         apply_staged(v);
         if (ADJ) apply_staged(w);
+       }
       } else if (on && active && type == OP_DIAG && ob) {
         // Entry by entry: one read of the entry, one of its two or four phases (and
         // weights), then each slot times the phase that its own bits, its lane's and the
@@ -766,11 +806,14 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
         // the amplitudes once; complex128 passes, where a second register block would cut the
         // resident waves, multiply the amplitudes entry by entry.
         constexpr bool gather = sizeof(R) == 4;
-        uint32_t flips = 0, touched = 0;
-        C ph[gather ? NR : 1];
-        double gws[gather && ADJ ? NR : 1];
+        constexpr int NG = gather && ADJ ? NR / 2 : NR;  // slots at a time
 #pragma unroll
-        for (int k = 0; k < (gather ? NR : 0); ++k) {
+       for (int kg = 0; kg < NR; kg += NG) {
+        uint32_t flips = 0, touched = 0;
+        C ph[gather ? NG : 1];
+        double gws[gather && ADJ ? NG : 1];
+#pragma unroll
+        for (int k = 0; k < (gather ? NG : 0); ++k) {
           ph[k] = C{1, 0};
           if (ADJ) gws[k] = 0.0;
         }
@@ -804,8 +847,8 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
             if constexpr (gather) {
               const double gs = in ? gw : 0.0;
 #pragma unroll
-              for (int k = 0; k < NR; ++k) {
-                if (!((ks >> k) & 1u)) continue;
+              for (int k = 0; k < NG; ++k) {
+                if (!((ks >> (kg + k)) & 1u)) continue;
                 ph[k] = cmul(ph[k], p);
                 if (ADJ) gws[k] += gs;
               }
@@ -827,17 +870,18 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
           }
         }
 #pragma unroll
-        for (int k = 0; k < NR; ++k) {
+        for (int i = 0; i < NG; ++i) {
+          const int k = kg + i;
           const uint32_t f = (flips << (31 - k)) & 0x80000000u;
           if constexpr (gather) {
-            flip_sign(ph[k], f);
+            flip_sign(ph[i], f);
             if (ADJ) {
-              double g = gws[k] * im_conj_mul(w[k], v[k]);
-              cmul_in(w[k], ph[k], g);
-              cmul_in(v[k], ph[k], g);
+              double g = gws[i] * im_conj_mul(w[k], v[k]);
+              cmul_in(w[k], ph[i], g);
+              cmul_in(v[k], ph[i], g);
               acc += g;
             } else {
-              cmul_in(v[k], ph[k]);
+              cmul_in(v[k], ph[i]);
             }
           } else {
             if (!((touched >> k) & 1u)) continue;
@@ -845,6 +889,7 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
             if (ADJ) flip_sign(w[k], f);
           }
         }
+       }
       } else if (on && active && type == OP_ZZ) {
         // c(x) = number of edges whose endpoints differ.  Edges come grouped by register
         // class c; an edge of class c differs in slot k iff its thread/outside parity
@@ -935,14 +980,14 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
   }
 }
 
-template <typename R, int RB, int MAXM, bool ADJ>
-__global__ __launch_bounds__(1 << (MAXM - RB)) void tile_pass_rb(PassArgs A) {
+template <typename R, int RB, int MAXM, bool ADJ, bool SPLIT>
+__global__ __launch_bounds__(1 << (MAXM - RB), SPLIT ? kSplitWaves : 1) void tile_pass_rb(PassArgs A) {
   // Workgroups go to the 8 XCDs in turn; give each XCD a contiguous range of tiles, so
   // tiles that share cache lines (they differ only in low qubits outside the tile) run
   // back to back behind the same L2.
   const uint32_t g = gridDim.x, w = blockIdx.x;
   const uint64_t t = (g % 8 == 0) ? (uint64_t)(w & 7) * (g >> 3) + (w >> 3) : w;
-  rb_body<R, RB, MAXM, ADJ, true>(A, t, blockIdx.y);
+  rb_body<R, RB, MAXM, ADJ, true, SPLIT>(A, t, blockIdx.y);
 }
 
 // Many circuits in one launch: item i owns workgroups [prefix[i], prefix[i+1]); each
@@ -966,7 +1011,14 @@ static hipError_t rb_launch_one(const PassArgs& A, dim3 grid, hipStream_t s) {
   // four register bits: complex64 forward passes only (their registers allow 4 waves/SIMD)
   if constexpr (bytes <= 131072 && (RB == 3 || (!ADJ && sizeof(R) == 4 && MAXM >= 10))) {
     const size_t dyn = rb_dyn_lds<R>(MAXM, ADJ, A.win_n, A.pass_pslots);
-    tile_pass_rb<R, RB, MAXM, ADJ><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
+    if constexpr (!ADJ) {
+      if (A.half_remap) {
+        tile_pass_rb<R, RB, MAXM, ADJ, true><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
+        return hipGetLastError();
+      }
+    }
+    if (A.half_remap) return hipErrorInvalidValue;
+    tile_pass_rb<R, RB, MAXM, ADJ, false><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;

@@ -79,3 +79,43 @@ def test_phase_runs_and_their_gradients(dtype, n, tile, adj):
     assert np.max(np.abs(g - g0)) <= TOL[dtype] * scale
     Q.qsv_apply_circuit(s, circ, params)
     assert np.max(np.abs(Q.qsv_state_get(s) - O.simulate(circ, params))) <= TOL[dtype]
+
+
+def _chain_gates(n, layers, rng):
+    """One-qubit gates of every form (identity-like and X-like ones among them) between CZs:
+    chains of every pivot, across rounds, passes and normalizations."""
+    gates = []
+    for layer in range(layers):
+        for q in range(n):
+            kind = str(rng.choice(["MAT1", "U3", "RX", "RY", "H", "near", "far", "RZ", "S"]))
+            if kind in ("near", "far"):
+                e = float(rng.choice([0.0, 1e-9, 1e-3]))
+                c = np.sqrt(1 - e * e)
+                m = np.array([[c, -e], [e, c]]) if kind == "near" else np.array([[e, -c], [c, e]])
+                m = np.exp(1j * rng.uniform(0, 6)) * m * np.exp(1j * np.array([0.0, rng.uniform(0, 6)]))
+                gates.append(W.gate("MAT1", (q,), matrix=m))
+            elif kind == "MAT1":
+                gates.append(W.gate(kind, (q,), matrix=W.haar_unitary_2x2(rng)))
+            else:
+                angles = 3 if kind == "U3" else 1 if kind in ("RX", "RY", "RZ") else 0
+                par = tuple((-1, 0.0, float(rng.choice([0.0, np.pi / 2, np.pi, rng.uniform(-7, 7)])))
+                            for _ in range(angles))
+                gates.append(W.gate(kind, (q,), params=par))
+        for a in range(layer % 2, n - 1, 2):
+            gates.append(W.gate("Z", (a + 1,), ctrls=(a,)))
+        if layer % 7 == 6:  # a chain that a controlled gate ends
+            gates.append(W.gate("RY", (0,), ctrls=(n - 1,), params=((-1, 0.0, 0.4),)))
+    return gates
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("n,tile,layers", [(9, 9, 40), (11, 10, 40), (14, 11, 24), (20, 9, 6), (20, None, 20)])
+def test_gate_chains(dtype, n, tile, layers):
+    Q = _q()
+    rng = np.random.default_rng(n + layers)
+    circ = W.circuit(n, _chain_gates(n, layers, rng))
+    psi = W.random_state(n, rng, np.complex64 if dtype == "c64" else np.complex128)
+    ref = O.simulate(circ, None, psi.astype(np.complex128))
+    got = _run(Q, circ, psi, dtype, tile)
+    assert np.max(np.abs(got - ref)) <= TOL[dtype]
+    assert abs(np.linalg.norm(got.astype(np.complex128)) - np.linalg.norm(psi)) <= 100 * TOL[dtype]
