@@ -1267,20 +1267,18 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
     auto splittable = [&](int32_t i) {
       const Prim& pr = plan.prims[i];
       if (pr.type != P_DENSE1 || pr.cmask != 0) return false;
-      if (pr.recipe == M_GATE && c->gates[pr.gate].kind == QSV_GATE_X) return false;  // a swap
+      // Real and X-like matrices stay by themselves: 8 instructions per pair against a chain's
+      // 6, but a chain of RX alone (QAOA mixers) put energies 1.5 times further off.
+      if (matrix_form(pr, c) != 0) return false;
       if (pr.recipe != M_FUSED) return unitary(pr);
       for (int k = 0; k < pr.part_count; ++k)
         if (!unitary(plan.parts[pr.part_first + k])) return false;
       return true;
     };
-    // Vector instructions per amplitude pair: a chain's gates take 6 each and its last one 16;
-    // by themselves gates with real or X-like matrices take 8, others 16.
     std::vector<std::vector<int32_t>> run(n);  // each qubit's gates in a row that can join
     auto close = [&](int q) {
       const std::vector<int32_t>& r = run[q];
-      int alone = 0;
-      for (int32_t i : r) alone += matrix_form(plan.prims[i], c) != 0 ? 8 : 16;
-      if (r.size() >= 2 && 6 * ((int)r.size() - 1) + 16 < alone) {
+      if (r.size() >= 2) {
         for (int32_t i : r) chain[i] = 1;
         chain[r.back()] = 2;
       }
