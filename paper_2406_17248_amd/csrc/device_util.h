@@ -172,6 +172,15 @@ template <typename C, typename... Pin> __device__ __forceinline__ void cmul_in(C
   a.y = fma_v(p.x, a.y, pi);
 }
 
+// ... p wave-uniform
+template <typename C, typename... Pin> __device__ __forceinline__ void cmul_in_s(C& a, C p, Pin&... pin) {
+  auto pr = -a.y * p.y;
+  auto pi = a.x * p.y;
+  order(pr, pi, pin...);
+  a.x = fma_s(p.x, a.x, pr);
+  a.y = fma_s(p.x, a.y, pi);
+}
+
 // Negate v when f is 0x80000000 (f = 0: unchanged), by flipping the sign bits.
 __device__ __forceinline__ void flip_sign(float2& v, uint32_t f) {
   v.x = __uint_as_float(__float_as_uint(v.x) ^ f);

@@ -840,6 +840,8 @@ struct PassEmitter {
         for (int k = 0; k < (1 << lay.r); ++k) bits |= (uint32_t)((k >> slot) & 1) << k;
       (b ? d.bits1 : d.bits0) = bits;
       d.where |= (q < 0 || slot >= 0 ? kNoBit : l >= 0 ? (uint32_t)l : 32u + (uint32_t)q) << (8 * b);
+      if (b == 0 && d.q1 < 0 && d.kind == DIAG_PHASE && d.cmask == 0)
+        d.where |= kWhereOne | (uint32_t)(slot + 1) << 24;
     }
   }
   // A ZZ edge with its thread-bit mask, outside-bit mask and (in pad, until the run is
@@ -1151,6 +1153,13 @@ struct PassEmitter {
       op.count = (int32_t)(plan.diag.size() - op.first);
       // register passes: sign-only runs take the kernel's short path
       if (rb && op.b == 0 && run_param < 0) op.plain = kPlainSigns;
+      if (rb && adjoint && op.b) {
+        op.plain = kPlainPhases;
+        if (op.count == 1) {
+          op.mat = plan.diag[op.first].mat;
+          op.gen = plan.diag[op.first].gen;
+        }
+      }
       push(op, run_param);
       k = e;
     }
@@ -1308,11 +1317,11 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
     dp.pslot_first = plan.n_pslots;
     PassEmitter em{plan, c, adjoint, opt, ps.tile_mask, {}, {}};
     if (rb && opt.half_remap && !adjoint) {
-      dp.half_remap = 1;
+      dp.alt = 1;
       for (int32_t i : ps.prims)
-        if (plan.prims[i].type == P_DENSE2) dp.half_remap = 0;
+        if (plan.prims[i].type == P_DENSE2) dp.alt = 0;
     }
-    em.row_bits = (opt.dtype == QSV_C64 ? 4 : 3) + (dp.half_remap ? 1 : 0);
+    em.row_bits = (opt.dtype == QSV_C64 ? 4 : 3) + dp.alt;
     {
       int r = 0;
       for (int q = 0; q < 64; ++q) em.loc[q] = (ps.tile_mask >> q & 1) ? r++ : -1;
@@ -1582,6 +1591,12 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
       plan.n_pslots += dp.pslot_count;
     }
     dp.op_count = (int32_t)plan.ops.size() - dp.op_first;
+    for (int i = 0; rb && adjoint && i < dp.op_count; ++i) {
+      const TileOp& o = plan.ops[dp.op_first + i];
+      if ((o.plain & kPlainPhases) && o.count == 1 && (plan.diag[o.first].where & kWhereOne)) dp.alt = 1;
+    }
+    for (int i = 0; rb && adjoint && !dp.alt && i < dp.op_count; ++i)
+      plan.ops[dp.op_first + i].plain &= ~kPlainPhases;
     for (int i = 0; rb && i < reg_bits; ++i)
       dp.lay0_units |= (uint64_t)lds_swizzle(1 << ((dp.lay0_reg >> (8 * i)) & 255), em.row_bits) << (16 * i);
     dp.ctab_n = plan.ctab_size - dp.ctab_lo;

@@ -143,7 +143,7 @@ struct DevPass {
   int32_t  dep_first;      // register-blocked: first of the pass's kDepEntries Plan::deps entries
   int32_t  relayout;       // register-blocked: stores go to another layout (and buffer)
   int32_t  ctab_lo, ctab_n, diag_lo, diag_n, edge_lo, edge_n;  // the pass's parts of the tables
-  int32_t  half_remap;     // register-blocked: remaps in two halves (see PassArgs)
+  int32_t  alt;            // register-blocked: variant (see PassArgs)
   uint64_t lay0_units;
 };
 
@@ -158,7 +158,7 @@ inline void set_table_parts(PassArgs& A, const DevPass& dp, int32_t warm) {
   A.edge_lo = dp.edge_lo;
   A.edge_n = dp.edge_n;
   A.warm = warm;
-  A.half_remap = dp.half_remap;
+  A.alt = dp.alt;
   A.lay0_units = dp.lay0_units;
 }
 

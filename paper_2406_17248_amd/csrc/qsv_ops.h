@@ -87,6 +87,9 @@ struct TileOp {
 constexpr int32_t kPlainSigns = 8, kPlainBlock = 16;
 constexpr int32_t kPlainSplit = 32, kPlainReal = 64, kPlainXlike = 96, kPlainForm = 96;
 constexpr int32_t kPlainFlip = 128, kPlainOutside = 256;
+// Reverse sweeps that have runs of a single one-qubit phase (PassArgs::alt): any run of diagonal
+// entries with phases among them; of a single entry, mat and gen repeat its table offsets.
+constexpr int32_t kPlainPhases = 512;
 static_assert(offsetof(TileOp, plain) == 0 && offsetof(TileOp, gkind) == 28 && alignof(TileOp) == 8,
               "plain .. gkind form the record's first 32 bytes");
 // Forms of split gates (see chain_gate): 0, any R and a phase p; else 1 + (p.y = 1 instead of
@@ -124,11 +127,13 @@ struct DiagEntry {
   // offsets again, and where the bits of q0 and q1 come from: bits0 / bits1 hold the slots
   // whose bit is 1 when the qubit is on a slot bit (else 0), byte 0 / 1 of `where` the
   // thread bit's local position, 32 + the global position of an outside bit, or kNoBit
-  // (slot bit, or no such qubit); bit 16 of `where`: SIGN entry, bit 17: two-qubit table.
+  // (slot bit, or no such qubit); bit 16 of `where`: SIGN entry, bit 17: two-qubit table,
+  // bit 18: one qubit and no controls, with 1 + the qubit's slot bit (0: not on a slot) in bits
+  // 24-26.
   int32_t  tab, gtab;
   uint32_t where, bits0, bits1, pad;
 };
-constexpr uint32_t kNoBit = 255, kWhereSign = 1u << 16, kWhereTwo = 1u << 17;
+constexpr uint32_t kNoBit = 255, kWhereSign = 1u << 16, kWhereTwo = 1u << 17, kWhereOne = 1u << 18;
 
 // One edge of an OP_ZZ run: global qubits (u, v) and their local bits in the pass's tile
 // (lu, lv; -1 when outside the tile).  For register-blocked passes, in the register layout
@@ -189,8 +194,10 @@ struct PassArgs {
   // [diag_lo, diag_lo + diag_n) and edges [edge_lo, edge_lo + edge_n)
   int32_t      ctab_lo, ctab_n, diag_lo, diag_n, edge_lo, edge_n;
   int32_t      warm;          // 1: read these ahead of their use
-  int32_t      half_remap;    // 1: remaps move real and imaginary parts separately (the LDS
-                              // terms below and in OP_REMAP are for 8-byte elements)
+  int32_t      alt;           // the pass's variant (see rb_body): forward 1: remaps move real and
+                              // imaginary parts separately (the LDS terms below and in OP_REMAP
+                              // are for elements of that size); reverse sweep 1: it has runs of
+                              // a single one-qubit phase
   uint64_t     lay0_units;    // load layout: LDS address terms of its register bits
 };
 

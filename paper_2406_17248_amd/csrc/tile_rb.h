@@ -353,6 +353,42 @@ __device__ __forceinline__ void block_dispatch(int slot, C* v, const R* a) {
   }
 }
 
+// One-qubit phases of the reverse sweep: slots whose slot bit I is 0 times p0, the others times
+// p1 (wave-uniform), with the gradient weights g0 and g1; I = -1: every slot times p0 (per lane).
+template <int I, int NR, typename C>
+__device__ __forceinline__ void phase1(C* v, C* w, C p0, C p1, double g0, double g1, double& acc) {
+  double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+  for (int k = 0; k < NR; ++k) {
+    const bool one = I >= 0 && (k >> (I >= 0 ? I : 0)) & 1;
+    // Slot by slot: otherwise the products that the dispatch's cases share are formed for every
+    // slot before it (50 more registers, three waves per SIMD instead of four).
+    asm volatile("" : "+v"(v[k].x), "+v"(v[k].y), "+v"(w[k].x), "+v"(w[k].y));
+    double g = im_conj_mul(w[k], v[k]);
+    if constexpr (I < 0) {
+      cmul_in(w[k], p0, g);
+      cmul_in(v[k], p0, g);
+    } else {
+      cmul_in_s(w[k], one ? p1 : p0, g);
+      cmul_in_s(v[k], one ? p1 : p0, g);
+    }
+    (one ? s1 : s0) += g;
+  }
+  acc = I < 0 ? __builtin_fma(g0, s0, acc) : __builtin_fma(g0, s0, __builtin_fma(g1, s1, acc));
+}
+template <int RB, typename C>
+__device__ __forceinline__ void phase1_dispatch(int slot, C* v, C* w, C p0, C p1, double g0, double g1, double& acc) {
+  constexpr int NR = 1 << RB;
+  switch (slot) {
+    case 0: phase1<0, NR>(v, w, p0, p1, g0, g1, acc); break;
+    case 1: phase1<1, NR>(v, w, p0, p1, g0, g1, acc); break;
+    case 2: phase1<2, NR>(v, w, p0, p1, g0, g1, acc); break;
+    default:
+      if constexpr (RB > 3) phase1<(RB > 3 ? 3 : 0), NR>(v, w, p0, p1, g0, g1, acc);
+      break;
+  }
+}
+
 __device__ __forceinline__ int insert_zero(int t, int p) { return ((t >> p) << (p + 1)) | (t & ((1 << p) - 1)); }
 
 // Dynamic LDS of the register-blocked passes, sized per launch: the ctab window, then
@@ -435,11 +471,17 @@ __device__ __forceinline__ uint32_t sign_slots(const DiagEntry* d, int count, ui
 // step: 197 -> 142 ms (five waves 164, six 149; eight spill); 27 qubits in complex64: 14.8 ->
 // 13.9 ms.  In launches that leave the chip idle the two further barriers only cost (10-qubit
 // ansatz 231 -> 257 us); the reverse sweep's registers do not fit five waves.
-constexpr int kSplitWaves = 7;
-template <typename R, int RB, int MAXM, bool ADJ, bool FULL, bool SPLIT = false>
+template <typename R> constexpr int kSplitWaves = sizeof(R) == 4 ? 6 : 7;
+//
+// ONE (reverse sweeps with runs of a single uncontrolled one-qubit phase, as ansatz circuits have
+// them): those runs' straight lines, which QAOA sweeps would pay for in registers (92 instead of
+// 79 in complex64, five waves per SIMD instead of six: 2.4 %).
+// ALT: SPLIT in forward passes, ONE in reverse sweeps.
+template <typename R, int RB, int MAXM, bool ADJ, bool FULL, bool ALT>
 __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, const int b) {
   using C = typename CT<R>::T;
   static_assert(RB == 3 || RB == 4, "register blocks of three or four bits");
+  constexpr bool SPLIT = ALT && !ADJ, ONE = ALT && ADJ;
   constexpr int NT = 1 << (MAXM - RB);
   constexpr int NR = 1 << RB;
   using X = std::conditional_t<SPLIT, R, C>;    // what one exchange moves per amplitude
@@ -571,6 +613,10 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
     }
   }
   asm volatile("" :: "v"(warm));
+  // the value of an index bit that the thread's local index or the tile's base holds
+  auto lane_bit = [&](uint32_t src) -> bool {
+    return src < 32 ? ((uint32_t)jt >> src) & 1u : src < kNoBit && ((base >> (src - 32)) & 1);
+  };
   double acc = 0.0;
   const TileOp* O = A.ops;
   for (int oi = 0; oi < A.n_ops; ++oi, ++O) {
@@ -581,7 +627,7 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
     const int first = (int)(uint32_t)h1, count = (int)(h1 >> 32);
     const int gen = (int)(uint32_t)h2, pslot = (int)(h2 >> 32);
     const int flush = (int)(uint32_t)h3, gkind = (int)(h3 >> 32);
-    if (plain) {
+    if (ONE ? plain && !(plain & kPlainPhases) : plain) {
       // the short path: a run of sign flips, then a one-qubit gate on a register slot or a
       // fused block (or nothing), with nothing else to decode
       const int slot = (plain & 7) - 1;
@@ -657,8 +703,13 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
         }
       }
     } else {
-      const int type = ld(&O->type);
-      const uint32_t lm_raw = ld(&O->lmask);
+      int type = OP_DIAG, ob = 1;  // (a run with phases: nothing else to read)
+      uint32_t lm_raw = 0;
+      if (!ONE || !plain) {
+        type = ld(&O->type);
+        lm_raw = ld(&O->lmask);
+        ob = ld(&O->b);
+      }
       bool on = true;
       if (lm_raw & kHasOutsideControls) {
         const uint64_t omask = ld(&O->omask);
@@ -668,7 +719,6 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
       // sign flips only (Z, CZ, multi-controlled Z), alone (DIAG with b = 0) or ahead of a
       // gate (DENSE1 with b = 1): the parity of the satisfied entries, as one bit per
       // register slot (slot 0 holds the thread's own local index)
-      const int ob = ld(&O->b);
       if (on && active && ((type == OP_DIAG && !ob) || (type == OP_DENSE1 && ob))) {
         uint32_t touched;
         const uint32_t sm = sign_slots(A.diag + first, count, base, (uint32_t)jt, touched);
@@ -807,6 +857,33 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
         // resident waves, multiply the amplitudes entry by entry.
         constexpr bool gather = sizeof(R) == 4;
         constexpr int NG = gather && ADJ ? NR / 2 : NR;  // slots at a time
+        // The reverse sweep's runs are mostly one uncontrolled one-qubit phase each (every run has
+        // one parameter): its numbers are read along with its entry, and slot-resident qubits
+        // take one straight line per slot bit instead of a test per slot.  10-qubit ansatz 230 ->
+        // 192 us, 20-qubit ansatz gradients (6 layers, 4 sets, complex64) 1837 -> 1539 us.
+        bool done = false;
+        if constexpr (ONE) {
+          if (count == 1) {
+            const C q0 = ldc(T + mat), q1 = ldc(T + mat + 1);
+            double w0 = 0.0, w1 = 0.0;
+            if (gen >= 0) {
+              w0 = (double)ldc(T + gen).x;
+              w1 = (double)ldc(T + gen + 1).x;
+            }
+            const PhaseFields f = ld_record(reinterpret_cast<const PhaseFields*>(&A.diag[first].ocmask));
+            if (f.where & kWhereOne) {
+              const int at = (int)(f.where >> 24) - 1;
+              if (at < 0) {  // the same phase in every slot
+                const bool t = lane_bit(f.where & 255u);
+                phase1<-1, NR>(v, w, csel(t, q1, q0), q1, t ? w1 : w0, 0.0, acc);
+              } else {
+                phase1_dispatch<RB>(at, v, w, q0, q1, w0, w1, acc);
+              }
+              done = true;
+            }
+          }
+        }
+       if (!done) {
 #pragma unroll
        for (int kg = 0; kg < NR; kg += NG) {
         uint32_t flips = 0, touched = 0;
@@ -827,10 +904,7 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
             continue;
           }
           const bool two = (f.where & kWhereTwo) != 0, grad = ADJ && f.gtab >= 0;
-          auto bit_at = [&](uint32_t src) -> bool {
-            return src < 32 ? ((uint32_t)jt >> src) & 1u : src < kNoBit && ((base >> (src - 32)) & 1);
-          };
-          const bool t0 = bit_at(f.where & 255u), t1 = bit_at((f.where >> 8) & 255u);
+          const bool t0 = lane_bit(f.where & 255u), t1 = lane_bit((f.where >> 8) & 255u);
           for (uint32_t u = 0; u < 4; ++u) {
             if (((u & 1) && !f.bits0) || ((u & 2) && !f.bits1)) continue;
             const uint32_t ks = f.kmask & ((u & 1) ? f.bits0 : ~f.bits0) & ((u & 2) ? f.bits1 : ~f.bits1);
@@ -889,6 +963,7 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
             if (ADJ) flip_sign(w[k], f);
           }
         }
+       }
        }
       } else if (on && active && type == OP_ZZ) {
         // c(x) = number of edges whose endpoints differ.  Edges come grouped by register
@@ -980,14 +1055,14 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
   }
 }
 
-template <typename R, int RB, int MAXM, bool ADJ, bool SPLIT>
-__global__ __launch_bounds__(1 << (MAXM - RB), SPLIT ? kSplitWaves : 1) void tile_pass_rb(PassArgs A) {
+template <typename R, int RB, int MAXM, bool ADJ, bool ALT>
+__global__ __launch_bounds__(1 << (MAXM - RB), ALT && !ADJ ? kSplitWaves<R> : 1) void tile_pass_rb(PassArgs A) {
   // Workgroups go to the 8 XCDs in turn; give each XCD a contiguous range of tiles, so
   // tiles that share cache lines (they differ only in low qubits outside the tile) run
   // back to back behind the same L2.
   const uint32_t g = gridDim.x, w = blockIdx.x;
   const uint64_t t = (g % 8 == 0) ? (uint64_t)(w & 7) * (g >> 3) + (w >> 3) : w;
-  rb_body<R, RB, MAXM, ADJ, true, SPLIT>(A, t, blockIdx.y);
+  rb_body<R, RB, MAXM, ADJ, true, ALT>(A, t, blockIdx.y);
 }
 
 // Many circuits in one launch: item i owns workgroups [prefix[i], prefix[i+1]); each
@@ -1002,7 +1077,7 @@ __global__ __launch_bounds__(1 << (MAXM - RB)) void tile_pass_rb_multi(const Pas
     if (ld(prefix + mid) <= w) lo = mid; else hi = mid;
   }
   const PassArgs A = items[lo];
-  rb_body<R, RB, MAXM, ADJ, false>(A, (uint64_t)(w - ld(prefix + lo)), 0);
+  rb_body<R, RB, MAXM, ADJ, false, ADJ>(A, (uint64_t)(w - ld(prefix + lo)), 0);
 }
 
 template <typename R, int RB, int MAXM, bool ADJ>
@@ -1011,14 +1086,8 @@ static hipError_t rb_launch_one(const PassArgs& A, dim3 grid, hipStream_t s) {
   // four register bits: complex64 forward passes only (their registers allow 4 waves/SIMD)
   if constexpr (bytes <= 131072 && (RB == 3 || (!ADJ && sizeof(R) == 4 && MAXM >= 10))) {
     const size_t dyn = rb_dyn_lds<R>(MAXM, ADJ, A.win_n, A.pass_pslots);
-    if constexpr (!ADJ) {
-      if (A.half_remap) {
-        tile_pass_rb<R, RB, MAXM, ADJ, true><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
-        return hipGetLastError();
-      }
-    }
-    if (A.half_remap) return hipErrorInvalidValue;
-    tile_pass_rb<R, RB, MAXM, ADJ, false><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
+    if (A.alt) tile_pass_rb<R, RB, MAXM, ADJ, true><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
+    else tile_pass_rb<R, RB, MAXM, ADJ, false><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
