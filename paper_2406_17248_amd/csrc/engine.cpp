@@ -6,7 +6,7 @@
 #include <cstdint>
 #include <cstring>
 #include <map>
-#include <sstream>
+#include <string>
 
 namespace qsv {
 
@@ -355,31 +355,30 @@ void validate_circuit(const qsv_circuit* c, size_t n_params, int32_t n_state) {
   const uint64_t full = (1ull << n) - 1;
   for (size_t i = 0; i < c->n_gates; ++i) {
     const qsv_gate& g = c->gates[i];
-    std::ostringstream where;
-    where << "gate " << i << ": ";
-    if (g.kind < 0 || g.kind >= QSV_GATE_KIND_COUNT) fail(QSV_EINVAL, where.str() + "unknown kind");
+    const auto where = [i] { return "gate " + std::to_string(i) + ": "; };
+    if (g.kind < 0 || g.kind >= QSV_GATE_KIND_COUNT) fail(QSV_EINVAL, where() + "unknown kind");
     const int nt = kNTargets[g.kind];
     for (int t = 0; t < nt; ++t)
-      if (g.targets[t] < 0 || g.targets[t] >= n) fail(QSV_EINVAL, where.str() + "target out of range");
-    if (nt == 2 && g.targets[0] == g.targets[1]) fail(QSV_EINVAL, where.str() + "duplicate targets");
-    if (g.ctrl_mask & ~full) fail(QSV_EINVAL, where.str() + "control out of range");
-    if (g.ctrl_mask & target_mask(g)) fail(QSV_EINVAL, where.str() + "control on a target");
+      if (g.targets[t] < 0 || g.targets[t] >= n) fail(QSV_EINVAL, where() + "target out of range");
+    if (nt == 2 && g.targets[0] == g.targets[1]) fail(QSV_EINVAL, where() + "duplicate targets");
+    if (g.ctrl_mask & ~full) fail(QSV_EINVAL, where() + "control out of range");
+    if (g.ctrl_mask & target_mask(g)) fail(QSV_EINVAL, where() + "control on a target");
     for (int a = 0; a < 3; ++a) {
       if (a < kNAngles[g.kind]) {
         if (g.param_index[a] < -1 || (g.param_index[a] >= 0 && (size_t)g.param_index[a] >= n_params))
-          fail(QSV_EINVAL, where.str() + "param_index out of range");
+          fail(QSV_EINVAL, where() + "param_index out of range");
         if (!std::isfinite(g.angle_const[a]) || !std::isfinite(g.param_coeff[a]))
-          fail(QSV_EINVAL, where.str() + "non-finite angle");
+          fail(QSV_EINVAL, where() + "non-finite angle");
       } else if (g.param_index[a] != -1) {
-        fail(QSV_EINVAL, where.str() + "unused angle slot must have param_index -1");
+        fail(QSV_EINVAL, where() + "unused angle slot must have param_index -1");
       }
     }
     if (g.kind == QSV_GATE_MAT1 || g.kind == QSV_GATE_MAT2) {
       const int64_t need = g.kind == QSV_GATE_MAT1 ? 4 : 16;
       if (!c->matrices || g.matrix_offset < 0 || (uint64_t)(2 * (g.matrix_offset + need)) > c->n_matrix_doubles)
-        fail(QSV_EINVAL, where.str() + "matrix out of range");
+        fail(QSV_EINVAL, where() + "matrix out of range");
       for (int k = 0; k < 2 * need; ++k)
-        if (!std::isfinite(c->matrices[2 * g.matrix_offset + k])) fail(QSV_EINVAL, where.str() + "non-finite matrix");
+        if (!std::isfinite(c->matrices[2 * g.matrix_offset + k])) fail(QSV_EINVAL, where() + "non-finite matrix");
     }
   }
 }
@@ -1682,6 +1681,7 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
 
 std::string structure_key(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
   std::string key;
+  key.reserve(64 + 56 * c->n_gates);
   auto put = [&](const void* p, size_t n) { key.append(reinterpret_cast<const char*>(p), n); };
   const int32_t head[14] = {c->n_qubits, adjoint ? 1 : 0, opt.tile_qubits, opt.low_qubits, opt.fuse_zz ? 1 : 0,
                             opt.dtype, opt.use_rb ? 1 : 0, opt.rb_min, opt.reg_bits, opt.relayout ? 1 : 0,
@@ -1847,6 +1847,29 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
   std::vector<double> ang(3 * c->n_gates);
   for (size_t i = 0; i < c->n_gates; ++i) gate_angles(c->gates[i], params, &ang[3 * i]);
   for (int k = 0; k < n_ov; ++k) ang[3 * ov[k].gate + ov[k].slot] = ov[k].angle;
+  // The last one-angle gate's numbers: a layer's gates often share their angle (QAOA mixers), and
+  // their sines and cosines are most of the work of binding a batch (16 qubits, 6 layers: 14 -> 6 us
+  // a row for the reverse sweep).
+  struct {
+    int kind = -1, dagger = 0, count = 0;
+    double angle = 0.0;
+    cplx v[16];
+  } last;
+  auto numbers = [&](const Prim& pr, cplx* dst) {
+    const int kind = pr.recipe == M_GATE ? c->gates[pr.gate].kind : -1;
+    if (kind < 0 || kNAngles[kind] != 1) {
+      prim_numbers(pr, p.parts, c, ang.data(), dst);
+      return;
+    }
+    const double a = ang[3 * pr.gate];
+    if (last.kind != kind || last.dagger != (int)pr.dagger || last.angle != a) {
+      last.kind = kind;
+      last.dagger = pr.dagger;
+      last.angle = a;
+      last.count = prim_numbers(pr, p.parts, c, ang.data(), last.v);
+    }
+    std::copy(last.v, last.v + last.count, dst);
+  };
   // phase chains: the left diagonal each qubit carries to its next gate, and its gates since the
   // diagonal's moduli were last folded in
   std::vector<int> gates_since((size_t)c->n_qubits, 0);
@@ -1872,8 +1895,7 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
         break;
       }
       case F_PRIM_MATRIX: {
-        const Prim& pr = p.prims[f.prim];
-        prim_numbers(pr, p.parts, c, ang.data(), dst);
+        numbers(p.prims[f.prim], dst);
         break;
       }
       case F_PRIM_GEN:
@@ -1883,7 +1905,10 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
         const Prim& pr = p.prims[f.prim];
         const double th = ang[3 * pr.gate];
         const double sgn = pr.dagger ? 1.0 : -1.0;
-        for (int cc = 0; cc <= f.count; ++cc) dst[cc] = std::polar(1.0, sgn * 0.5 * th * (f.count - 2 * cc));
+        for (int cc = 0; 2 * cc <= f.count; ++cc) {  // entry count - cc is the conjugate of entry cc
+          dst[cc] = std::polar(1.0, sgn * 0.5 * th * (f.count - 2 * cc));
+          if (2 * cc < f.count) dst[f.count - cc] = std::conj(dst[cc]);
+        }
         break;
       }
       case F_ZZ_GEN: {

@@ -119,3 +119,25 @@ def test_gate_chains(dtype, n, tile, layers):
     got = _run(Q, circ, psi, dtype, tile)
     assert np.max(np.abs(got - ref)) <= TOL[dtype]
     assert abs(np.linalg.norm(got.astype(np.complex128)) - np.linalg.norm(psi)) <= 100 * TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("n", [3, 10])
+def test_neighbours_that_share_an_angle(dtype, n):
+    """Gates of one kind and of several with equal angles, side by side, and what the reverse
+    sweep makes of them: each gets its own numbers."""
+    Q = _q()
+    gates = [W.gate("H", (q,)) for q in range(n)]
+    for kinds in (["RX", "RX", "RY", "RY", "RX"], ["RZ", "PS", "RZ", "RZZ", "RZZ", "RY"], ["PS", "RX", "PS"]):
+        for i, k in enumerate(kinds):
+            qs = tuple((i + j) % n for j in range(2 if k == "RZZ" else 1))
+            gates.append(W.gate(k, qs, params=((0, 1.0, 0.0),)))
+        gates.append(W.gate("Z", (1,), ctrls=(0,)))
+    circ = W.circuit(n, gates)
+    ham = W.random_pauli_sum(n, 5, np.random.default_rng(n))
+    s = Q.qsv_state_create(n, dtype)
+    e, g = Q.qsv_expectation_and_grad(s, circ, ham, np.array([0.83]))
+    e0, g0 = O.grad_adjoint(circ, ham, np.array([0.83]))
+    scale = max(1.0, sum(abs(c) for c, _ in ham)) * len(gates)
+    assert abs(e - e0) <= TOL[dtype] * scale
+    assert np.max(np.abs(g - g0)) <= TOL[dtype] * scale
