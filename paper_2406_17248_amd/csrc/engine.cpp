@@ -324,13 +324,12 @@ PlanOptions state_plan_options(int32_t dtype, int32_t n, int32_t tile, int32_t a
   // complex64 forward passes keep 16 amplitudes per thread (registers still allow 4 waves
   // per SIMD): fewer REMAPs and half the per-op and per-tile work per amplitude
   if (!adjoint && dtype == QSV_C64) o.reg_bits = 4;
-  // forward passes fuse three-qubit rounds of one-qubit gates into matrix-core blocks,
-  // keeping a round's blocks when they average enough gates.  complex64: fp32 matrix cores
-  // run at twice the rate of the (unpacked) fp32 vector ALU, so a block of 16x16x4 products
-  // costs about two register gates plus its layout moves; 3 is the best threshold of
-  // 2 / 2.5 / 3 / 3.5 on the brick and QAOA circuits.  complex128: fp64 matrix and vector
-  // rates are equal, so a block costs about four gates, but the matrix cores run beside the
-  // vector ALU's other work; 4.5 is the best of 3.5 / 4.5 / 5.5 / none (brick: -7 %).
+  // complex64 forward passes fuse three-qubit rounds of one-qubit gates into matrix-core blocks,
+  // keeping a round's blocks when they average enough gates: fp32 matrix cores run at twice the
+  // rate of the (unpacked) fp32 vector ALU, so a block of 16x16x4 products costs about two
+  // register gates plus its layout moves; 3 is the best threshold of 2 / 2.5 / 3 / 3.5 on the
+  // brick and QAOA circuits.  complex128: fp64 matrix and vector rates are equal, so a block
+  // costs as much as four gates of 16 instructions, or ten in a chain (below).
   o.blocks = !adjoint && dtype == QSV_C64;
   o.block_min_gates = 3.0;
   // complex128 forward passes fuse a qubit's one-qubit gates and split them: a phase and a real
@@ -339,7 +338,8 @@ PlanOptions state_plan_options(int32_t dtype, int32_t n, int32_t tile, int32_t a
   // error in the amplitudes, but energies came out 1.4 times further off: fewer gate matrices
   // are rounded to 32 bits in the blocks.)
   o.split = o.fuse1 = !adjoint && dtype == QSV_C128;
-  // (rb_body's SPLIT: more resident waves pay once there are more workgroups than fit)
+  // (rb_body's SPLIT: more resident waves pay once there are more workgroups than fit on the
+  // chip at four waves per SIMD: 30 qubits 197 -> 142 ms, a 10-qubit ansatz 231 -> 257 us)
   const int m = std::min<int>(std::max(o.tile_qubits, 2), n);
   o.half_remap = !adjoint && (batch << (n - m)) > kWarmTiles;
   return o;

@@ -214,8 +214,8 @@ struct PlanOptions {
                               // one-qubit gates followed on their qubit by another such gate
                               // run as a phase and a real 2x2 matrix; the rest of the gate (a
                               // diagonal) is carried into the qubit's next gate
-  bool    half_remap = false; // complex128 forward register-blocked passes without two-qubit
-                              // matrices remap in two halves, through half the LDS
+  bool    half_remap = false; // forward register-blocked passes without two-qubit matrices remap
+                              // in two halves, through half the LDS (launches of many tiles)
   bool    fuse1 = false;      // forward plans: one-qubit gates and phases of one qubit with
                               // nothing but diagonal gates between them run as one gate
 };

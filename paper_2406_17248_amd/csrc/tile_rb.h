@@ -467,15 +467,17 @@ __device__ __forceinline__ uint32_t sign_slots(const DiagEntry* d, int count, ui
 // real and the imaginary parts one after the other through half the LDS.  A pass waits more
 // than it computes (scalar loads, branches, remaps: with four waves per SIMD the vector ALU
 // was busy 56 % of the time), so it wants resident waves: half the exchange buffer and 72
-// registers allow seven per SIMD where LDS allowed four.  30-qubit brick in complex128, whole
-// step: 197 -> 142 ms (five waves 164, six 149; eight spill); 27 qubits in complex64: 14.8 ->
-// 13.9 ms.  In launches that leave the chip idle the two further barriers only cost (10-qubit
-// ansatz 231 -> 257 us); the reverse sweep's registers do not fit five waves.
+// registers allow seven per SIMD in complex128 where LDS allowed four (complex64, 16 amplitudes
+// a thread: six).  30-qubit brick in complex128, whole step: 197 -> 142 ms (five waves 164, six
+// 149; eight spill); 27 qubits in complex64: 14.8 -> 13.9 ms.  In launches that leave the chip
+// idle the two further barriers only cost (10-qubit ansatz 231 -> 257 us); the reverse sweep's
+// registers spill at five waves (24-qubit QAOA gradients 46 -> 54 ms).
 template <typename R> constexpr int kSplitWaves = sizeof(R) == 4 ? 6 : 7;
-//
+
 // ONE (reverse sweeps with runs of a single uncontrolled one-qubit phase, as ansatz circuits have
 // them): those runs' straight lines, which QAOA sweeps would pay for in registers (92 instead of
-// 79 in complex64, five waves per SIMD instead of six: 2.4 %).
+// 79 in complex64, five waves per SIMD instead of six: 2.4 %).  10-qubit ansatz gradient 230 ->
+// 195 us, 48 uneven ansatz circuits 2570 -> 2200 us; a 20-qubit one 1830 -> 1510 us.
 // ALT: SPLIT in forward passes, ONE in reverse sweeps.
 template <typename R, int RB, int MAXM, bool ADJ, bool FULL, bool ALT>
 __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, const int b) {
