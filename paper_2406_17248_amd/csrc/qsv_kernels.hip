@@ -334,14 +334,57 @@ __global__ __launch_bounds__(256) void broadcast_state(void* dst_, int64_t bstri
 }
 
 // ------------------------------------------------------------------------------------------
-// Multi-circuit Pauli-sum pass in gather form: each thread owns an output index y and sums
+// Multi-circuit Pauli-sum pass in gather form: each thread owns output indices y and sums
 // c_k P_k psi over all terms, (P_k psi)[y] = i^{popcount(x_k & z_k)} (-1)^{popcount((y ^ x_k) & z_k)}
 // psi[y ^ x_k]; no two threads write the same lambda entry, so one launch covers every
 // term.  Workgroup w handles chunk (w - prefix[i]) of job i (CHUNK amplitudes).
+// A term's numbers and its load are two dependent round trips, which bound the pass: a thread
+// takes NY outputs, 256 apart, through each term together, so that NY loads wait at once and
+// the parity of the thread's own bits is formed once.  48 circuits of 8 to 16 qubits, complex64:
+// 224 -> 93 us.  Circuits of less than 256 NY amplitudes take one output at a time.
 // ------------------------------------------------------------------------------------------
+template <int NY, typename C>
+__device__ __forceinline__ void pauli_outputs(const PauliJob* J, const C* psi, C* lam, const uint64_t y0,
+                                              double& er, double& ei) {
+  const uint64_t* xm = ld(&J->xmasks);
+  const uint64_t* zm = ld(&J->zmasks);
+  const double* cre = ld(&J->cre);
+  const double* cim = ld(&J->cim);
+  const int nt = ld(&J->n_terms);
+  double lr[NY] = {}, li[NY] = {};
+  for (int k = 0; k < nt; ++k) {
+    const uint64_t x0 = y0 ^ ld(xm + k), z = ld(zm + k);
+    C v[NY];
+#pragma unroll
+    for (int j = 0; j < NY; ++j) v[j] = psi[x0 ^ ((uint64_t)j << 8)];
+    const double sgn = (__popcll(x0 & z) & 1) ? -1.0 : 1.0;
+    const double ar0 = sgn * ld(cre + k), ai0 = sgn * ld(cim + k);
+#pragma unroll
+    for (int j = 0; j < NY; ++j) {
+      const bool neg = __popcll(z & ((uint64_t)j << 8)) & 1;  // wave-uniform
+      const double ar = neg ? -ar0 : ar0, ai = neg ? -ai0 : ai0;
+      lr[j] += ar * v[j].x - ai * v[j].y;
+      li[j] += ar * v[j].y + ai * v[j].x;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NY; ++j) {
+    const uint64_t y = y0 ^ ((uint64_t)j << 8);
+    const C py = psi[y];
+    er += (double)py.x * lr[j] + (double)py.y * li[j];
+    ei += (double)py.x * li[j] - (double)py.y * lr[j];
+    C o;
+    o.x = (decltype(o.x))lr[j];
+    o.y = (decltype(o.y))li[j];
+    lam[y] = o;
+  }
+}
+
 template <typename R, int CHUNK>
 __global__ __launch_bounds__(256) void pauli_apply_multi(const PauliJob* jobs, const uint32_t* prefix, int n_jobs) {
   using C = typename CT<R>::T;
+  constexpr int NY = 8;
+  static_assert(CHUNK % (256 * NY) == 0, "a chunk is whole groups of NY outputs per thread");
   __shared__ double red[2][4];
   const uint32_t w = blockIdx.x;
   int lo = 0, hi = n_jobs;
@@ -353,30 +396,14 @@ __global__ __launch_bounds__(256) void pauli_apply_multi(const PauliJob* jobs, c
   const uint32_t chunk = w - ld(prefix + lo);
   const C* psi = reinterpret_cast<const C*>(ld(&J->psi));
   C* lam = reinterpret_cast<C*>(ld(&J->lam));
-  const uint64_t* xm = ld(&J->xmasks);
-  const uint64_t* zm = ld(&J->zmasks);
-  const double* cre = ld(&J->cre);
-  const double* cim = ld(&J->cim);
-  const int nt = ld(&J->n_terms);
   const uint64_t N = 1ull << ld(&J->n_qubits);
+  const uint64_t first = (uint64_t)chunk * CHUNK;
+  const uint64_t last = first + CHUNK < N ? first + CHUNK : N;
   double er = 0.0, ei = 0.0;
-  for (uint64_t y = (uint64_t)chunk * CHUNK + threadIdx.x; y < N && y < (uint64_t)(chunk + 1) * CHUNK; y += 256) {
-    double lr = 0.0, li = 0.0;
-    for (int k = 0; k < nt; ++k) {
-      const uint64_t x = y ^ ld(xm + k);
-      const C v = psi[x];
-      const double sgn = (__popcll(x & ld(zm + k)) & 1) ? -1.0 : 1.0;
-      const double ar = sgn * ld(cre + k), ai = sgn * ld(cim + k);
-      lr += ar * v.x - ai * v.y;
-      li += ar * v.y + ai * v.x;
-    }
-    const C py = psi[y];
-    er += (double)py.x * lr + (double)py.y * li;
-    ei += (double)py.x * li - (double)py.y * lr;
-    C o;
-    o.x = (R)lr;
-    o.y = (R)li;
-    lam[y] = o;
+  if (N >= 256 * NY) {  // then last - first is a multiple of 256 NY
+    for (uint64_t y = first + threadIdx.x; y < last; y += 256 * NY) pauli_outputs<NY>(J, psi, lam, y, er, ei);
+  } else {
+    for (uint64_t y = first + threadIdx.x; y < last; y += 256) pauli_outputs<1>(J, psi, lam, y, er, ei);
   }
   er = wave_sum(er);
   ei = wave_sum(ei);

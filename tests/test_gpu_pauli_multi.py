@@ -67,3 +67,27 @@ def test_tiled_groups_match_one_group_at_a_time(Q, dtype, n):
     scale = max(1.0, sum(abs(c) for c, _ in h))
     assert abs(e - e_ref) <= TOL[dtype] * scale
     assert float((b - ref).abs().max()) <= TOL[dtype] * scale
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+def test_many_circuits_at_the_edges_of_their_chunks(dtype):
+    """H psi of circuits in one launch, one output or eight per thread: states below, at and above
+    2048 amplitudes and the chunk of 4096."""
+    import paper_2406_17248_amd as Q
+    rng = np.random.default_rng(31)
+    circs, hams = [], []
+    for n in (4, 7, 8, 9, 10, 11, 12, 13):  # batches start at 4 qubits
+        gates = [W.gate("RY", (q,), params=((0, 1.0, 0.1 * q),)) for q in range(n)]
+        gates += [W.gate("X", (q + 1,), ctrls=(q,)) for q in range(n - 1)]
+        gates += [W.gate("RX", (q,), params=((1, 1.0, 0.2 * q),)) for q in range(n)]
+        circs.append(W.circuit(n, gates))
+        hams.append(W.random_pauli_sum(n, 9, rng))
+    b = Q.qsv_batch_create(circs, hams, dtype)
+    params = rng.uniform(-np.pi, np.pi, 2 * len(circs))
+    e, g = Q.qsv_batch_expectation_and_grad(b, params)
+    tol = 1e-5 if dtype == "c64" else 1e-12
+    for i, (c, h) in enumerate(zip(circs, hams)):
+        e0, g0 = O.grad_adjoint(c, h, params[b.offsets[i]:b.offsets[i + 1]])
+        scale = max(1.0, sum(abs(x) for x, _ in h)) * c["n_qubits"]
+        assert abs(e[i] - e0) <= tol * scale, c["n_qubits"]
+        assert np.max(np.abs(g[b.offsets[i]:b.offsets[i + 1]] - g0)) <= tol * scale, c["n_qubits"]
