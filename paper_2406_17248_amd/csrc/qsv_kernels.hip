@@ -340,7 +340,7 @@ __global__ __launch_bounds__(256) void broadcast_state(void* dst_, int64_t bstri
 // term.  Workgroup w handles chunk (w - prefix[i]) of job i (CHUNK amplitudes).
 // A term's numbers and its load are two dependent round trips, which bound the pass: a thread
 // takes NY outputs, 256 apart, through each term together, so that NY loads wait at once and
-// the parity of the thread's own bits is formed once.  48 circuits of 8 to 16 qubits, complex64:
+// the parity of the thread's own bits is formed once.  48 circuits of 8 to 20 qubits, complex64:
 // 224 -> 93 us.  Circuits of less than 256 NY amplitudes take one output at a time.
 // ------------------------------------------------------------------------------------------
 template <int NY, typename C>
