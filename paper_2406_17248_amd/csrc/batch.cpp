@@ -107,7 +107,7 @@ void build(qsv_batch* b) {
   oa.tile_qubits = std::min<int>(b->tile, b->dtype == QSV_C64 ? 13 : 12);
   of.low_qubits = oa.low_qubits = b->low > 0 ? b->low : (b->dtype == QSV_C64 ? 4 : 3);
   of.dtype = oa.dtype = b->dtype;
-  of.split = of.fuse1 = b->dtype == QSV_C128;
+  of.split = b->dtype == QSV_C128;
   of.rb_min = oa.rb_min = 4;  // every pass register-blocked, small tiles with idle threads
   b->fwd.clear();
   b->adj.clear();

@@ -187,36 +187,7 @@ void dagger_numbers(int type, cplx* v, int count) {
   }
 }
 
-// ang: the bound angles of every gate, three each.
-int prim_numbers(const Prim& p, const std::vector<Prim>& parts, const qsv_circuit* c, const double* angles, cplx* out) {
-  if (p.recipe == M_FUSED) {
-    cplx m[4] = {1.0, 0.0, 0.0, 1.0};
-    for (int i = 0; i < p.part_count; ++i) {
-      const Prim& f = parts[p.part_first + i];
-      cplx u[4];
-      if (f.type == P_SIGN) {
-        u[0] = 1.0;
-        u[1] = -1.0;
-      } else {
-        prim_numbers(f, parts, c, angles, u);
-      }
-      if (f.type == P_DENSE1) {
-        const cplx t[4] = {u[0] * m[0] + u[1] * m[2], u[0] * m[1] + u[1] * m[3], u[2] * m[0] + u[3] * m[2],
-                           u[2] * m[1] + u[3] * m[3]};
-        for (int k = 0; k < 4; ++k) m[k] = t[k];
-      } else {
-        for (int k = 0; k < 4; ++k) m[k] *= u[k >> 1];
-      }
-    }
-    if (p.type == P_DENSE1) {
-      for (int k = 0; k < 4; ++k) out[k] = m[k];
-      return 4;
-    }
-    out[0] = m[0];
-    out[1] = m[3];
-    return 2;
-  }
-  const double* ang = angles + 3 * p.gate;
+int prim_numbers(const Prim& p, const qsv_circuit* c, const double* ang, cplx* out) {
   int cnt = 0;
   const double a = ang[p.angle_slot];
   switch (p.recipe) {
@@ -332,12 +303,14 @@ PlanOptions state_plan_options(int32_t dtype, int32_t n, int32_t tile, int32_t a
   // costs as much as four gates of 16 instructions, or ten in a chain (below).
   o.blocks = !adjoint && dtype == QSV_C64;
   o.block_min_gates = 3.0;
-  // complex128 forward passes fuse a qubit's one-qubit gates and split them: a phase and a real
-  // 2x2 matrix with unit entries cost 6 vector instructions per amplitude pair instead of 16.
-  // (complex64 ones ran 22 % faster than with the blocks on the 27-qubit brick, with the same
-  // error in the amplitudes, but energies came out 1.4 times further off: fewer gate matrices
-  // are rounded to 32 bits in the blocks.)
-  o.split = o.fuse1 = !adjoint && dtype == QSV_C128;
+  // complex128 forward passes split general one-qubit gates: a phase and a real 2x2 matrix with
+  // unit entries cost 6 vector instructions per amplitude pair instead of 16.  (complex64 ones
+  // ran 22 % faster than with the blocks on the 27-qubit brick, with the same error in the
+  // amplitudes, but energies came out 1.4 times further off: fewer gate matrices are rounded to
+  // 32 bits in the blocks.)  Each gate keeps its own numbers: the products of neighbours (RY RZ,
+  // H T) rounded to double save instructions, but put states up to 10 and norms up to 60 times
+  // further off than the gates one by one (24 layers on 9 qubits).
+  o.split = !adjoint && dtype == QSV_C128;
   // (rb_body's SPLIT: more resident waves pay once there are more workgroups than fit on the
   // chip at four waves per SIMD: 30 qubits 197 -> 142 ms, a 10-qubit ansatz 231 -> 257 us)
   const int m = std::min<int>(std::max(o.tile_qubits, 2), n);
@@ -501,68 +474,6 @@ std::vector<Prim> lower_adjoint(const qsv_circuit* c) {
       p.coeff = g.param_coeff[0];
     }
     out.push_back(p);
-  }
-  return out;
-}
-
-// One-qubit primitives of one qubit with nothing but diagonal primitives on it between them, as
-// one primitive: a phase (or Z) joins the one-qubit gate before it, or the next one after it;
-// a gate joins the one right before it.  Everything else keeps its order.
-static std::vector<Prim> fuse_one_qubit(const std::vector<Prim>& in, int n, std::vector<Prim>& parts) {
-  std::vector<Prim> out;
-  std::vector<std::vector<Prim>> own;               // parts of out's one-qubit primitives
-  std::vector<int> gate(n, -1), tail(n, -1);        // last gate of q since which q saw only
-                                                    // diagonal primitives; ... saw nothing
-  std::vector<std::vector<Prim>> held(n);           // phases of q that wait for its next gate
-  auto append = [&](const Prim& p, std::vector<Prim> f) {
-    out.push_back(p);
-    own.push_back(std::move(f));
-  };
-  auto release = [&](int q) {  // the waiting phases by themselves
-    if (held[q].empty()) return;
-    Prim d = held[q][0];
-    if (held[q].size() > 1) {
-      d.type = P_DIAG1;
-      d.cmask = 0;
-      d.touched = 1ull << q;
-    }
-    append(d, std::move(held[q]));
-    held[q].clear();
-  };
-  for (const Prim& p : in) {
-    const bool one = (p.type == P_DENSE1 || p.type == P_DIAG1) && p.cmask == 0;
-    const bool z = p.type == P_SIGN && popc(p.cmask) == 1;
-    const int q = z ? __builtin_ctzll(p.cmask) : p.q0;
-    if (one && p.type == P_DENSE1) {
-      if (tail[q] >= 0) {
-        own[tail[q]].push_back(p);
-        continue;
-      }
-      std::vector<Prim> f = std::move(held[q]);
-      held[q].clear();
-      f.push_back(p);
-      gate[q] = tail[q] = (int)out.size();
-      append(p, std::move(f));
-    } else if (one || z) {
-      if (gate[q] >= 0) own[gate[q]].push_back(p);
-      else held[q].push_back(p);
-    } else {
-      for (uint64_t t = p.touched; t; t &= t - 1) tail[__builtin_ctzll(t)] = -1;
-      for (uint64_t t = p.nondiag; t; t &= t - 1) {
-        release(__builtin_ctzll(t));
-        gate[__builtin_ctzll(t)] = -1;
-      }
-      append(p, {});
-    }
-  }
-  for (int q = 0; q < n; ++q) release(q);
-  for (size_t i = 0; i < out.size(); ++i) {
-    if (own[i].size() < 2) continue;
-    Prim& p = out[i];
-    p.recipe = M_FUSED;
-    p.part_first = (int32_t)parts.size();
-    p.part_count = (int32_t)own[i].size();
-    parts.insert(parts.end(), own[i].begin(), own[i].end());
   }
   return out;
 }
@@ -1182,7 +1093,6 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
   plan.n_qubits = c->n_qubits;
   plan.prims = adjoint ? lower_adjoint(c) : lower_forward(c);
   const int n = c->n_qubits;
-  if (!adjoint && opt.fuse1 && opt.tile_qubits != 0) plan.prims = fuse_one_qubit(plan.prims, n, plan.parts);
   auto alloc = [&](int count) {
     const int off = plan.ctab_size;
     plan.ctab_size += count;
@@ -1269,19 +1179,14 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
   // dense.
   std::vector<char> chain(plan.prims.size(), 0);
   if (rb && opt.split && !adjoint && !opt.blocks) {
-    auto unitary = [&](const Prim& pr) {
-      return pr.recipe != M_GATE || c->gates[pr.gate].kind != QSV_GATE_MAT1 || mat1_is_unitary(c, c->gates[pr.gate]);
-    };
     auto splittable = [&](int32_t i) {
       const Prim& pr = plan.prims[i];
       if (pr.type != P_DENSE1 || pr.cmask != 0) return false;
       // Real and X-like matrices stay by themselves: 8 instructions per pair against a chain's
       // 6, but a chain of RX alone (QAOA mixers) put energies 1.5 times further off.
       if (matrix_form(pr, c) != 0) return false;
-      if (pr.recipe != M_FUSED) return unitary(pr);
-      for (int k = 0; k < pr.part_count; ++k)
-        if (!unitary(plan.parts[pr.part_first + k])) return false;
-      return true;
+      const qsv_gate& g = c->gates[pr.gate];
+      return pr.recipe != M_GATE || g.kind != QSV_GATE_MAT1 || mat1_is_unitary(c, g);
     };
     std::vector<std::vector<int32_t>> run(n);  // each qubit's gates in a row that can join
     auto close = [&](int q) {
@@ -1683,9 +1588,9 @@ std::string structure_key(const qsv_circuit* c, bool adjoint, const PlanOptions&
   std::string key;
   key.reserve(64 + 56 * c->n_gates);
   auto put = [&](const void* p, size_t n) { key.append(reinterpret_cast<const char*>(p), n); };
-  const int32_t head[14] = {c->n_qubits, adjoint ? 1 : 0, opt.tile_qubits, opt.low_qubits, opt.fuse_zz ? 1 : 0,
+  const int32_t head[13] = {c->n_qubits, adjoint ? 1 : 0, opt.tile_qubits, opt.low_qubits, opt.fuse_zz ? 1 : 0,
                             opt.dtype, opt.use_rb ? 1 : 0, opt.rb_min, opt.reg_bits, opt.relayout ? 1 : 0,
-                            opt.blocks ? 1 : 0, opt.split ? 1 : 0, opt.fuse1 ? 1 : 0, opt.half_remap ? 1 : 0};
+                            opt.blocks ? 1 : 0, opt.split ? 1 : 0, opt.half_remap ? 1 : 0};
   put(head, sizeof(head));
   for (size_t i = 0; i < c->n_gates; ++i) {
     const qsv_gate& g = c->gates[i];
@@ -1745,7 +1650,7 @@ static void block_matrix(const Plan& p, const qsv_circuit* c, const std::vector<
   for (int32_t pi : b.prims) {
     const Prim& pr = p.prims[pi];
     cplx num[16];
-    prim_numbers(pr, p.parts, c, ang.data(), num);
+    prim_numbers(pr, c, &ang[3 * pr.gate], num);
     if (pr.type == P_DENSE1) {
       const int t = bit_of(pr.q0);
       for (int col = 0; col < 8; ++col)
@@ -1858,7 +1763,7 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
   auto numbers = [&](const Prim& pr, cplx* dst) {
     const int kind = pr.recipe == M_GATE ? c->gates[pr.gate].kind : -1;
     if (kind < 0 || kNAngles[kind] != 1) {
-      prim_numbers(pr, p.parts, c, ang.data(), dst);
+      prim_numbers(pr, c, &ang[3 * pr.gate], dst);
       return;
     }
     const double a = ang[3 * pr.gate];
@@ -1866,7 +1771,7 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
       last.kind = kind;
       last.dagger = pr.dagger;
       last.angle = a;
-      last.count = prim_numbers(pr, p.parts, c, ang.data(), last.v);
+      last.count = prim_numbers(pr, c, &ang[3 * pr.gate], last.v);
     }
     std::copy(last.v, last.v + last.count, dst);
   };
@@ -1880,7 +1785,7 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
       case F_GATE_CHAIN: {
         const Prim& pr = p.prims[f.prim];
         cplx M[4];
-        prim_numbers(pr, p.parts, c, ang.data(), M);
+        prim_numbers(pr, c, &ang[3 * pr.gate], M);
         cplx* cq = &carry[2 * (size_t)pr.q0];
         int& since = gates_since[pr.q0];
         if (f.count) {

@@ -36,8 +36,6 @@ enum MatRecipe : int32_t {
   M_RX_PLUS,     // RX(+pi/2) (basis change of a lowered RYY)
   M_RX_MINUS,    // RX(-pi/2)
   M_ZZ_ANGLE,    // diag(e^{-i a/2}, e^{i a/2}, e^{i a/2}, e^{-i a/2}), a = angle[0]
-  M_FUSED,       // the product of one-qubit primitives of one qubit: Plan::parts
-                 // [part_first, part_first + part_count), in execution order
 };
 
 enum PrimType : int32_t { P_DENSE1 = 0, P_DENSE2, P_DIAG1, P_DIAG2, P_SIGN };
@@ -56,7 +54,6 @@ struct Prim {
   // planning masks
   uint64_t nondiag;     // qubits acted on non-diagonally (must be tile qubits)
   uint64_t touched;     // every qubit involved (targets and controls)
-  int32_t  part_first = 0, part_count = 0;  // M_FUSED
 };
 
 struct Pass {
@@ -176,7 +173,6 @@ struct Plan {
   bool unfused = false;     // per-primitive streaming kernels
   int32_t n_qubits = 0;
   std::vector<Prim> prims;
-  std::vector<Prim> parts;  // of M_FUSED primitives
   std::vector<DevPass> passes;
   // register-blocked passes, kDepEntries per pass (layout in qsv_ops.h): where each local
   // index is read and written, and runs forming a tile's logical, load and store bases
@@ -216,8 +212,6 @@ struct PlanOptions {
                               // diagonal) is carried into the qubit's next gate
   bool    half_remap = false; // forward register-blocked passes without two-qubit matrices remap
                               // in two halves, through half the LDS (launches of many tiles)
-  bool    fuse1 = false;      // forward plans: one-qubit gates and phases of one qubit with
-                              // nothing but diagonal gates between them run as one gate
 };
 
 // Block index bit b of an 8x8 fused block and the real 16x16 matrix-core operands: the real
