@@ -1676,75 +1676,59 @@ static void block_matrix(const Plan& p, const qsv_circuit* c, const std::vector<
   }
 }
 
-void split_gate(const cplx* M, cplx* left, cplx* out) {
-  // M = diag(l0, l1) [[c, -s], [s, c]] diag(1, e^{i phi}) for unitary M: c = |M00| = |M11|,
-  // s = |M10| = |M01|; each phase comes from an entry of modulus at least 1/sqrt(2) where
-  // one exists, so rounding stays at the level of M's own.
-  const double a = std::abs(M[0]), b = std::abs(M[2]), nrm = std::hypot(a, b);
-  const double cs = a / nrm, sn = b / nrm;
-  cplx l0, l1, ph(1.0, 0.0);
-  auto unit = [](cplx z) { return z / std::abs(z); };
-  if (a >= b) {
-    l0 = unit(M[0]);
-    if (b > 0.0) {
-      l1 = unit(M[2]);
-      ph = unit(M[3] / l1);
-    } else {
-      l1 = unit(M[3]);
-    }
-  } else {
-    l1 = unit(M[2]);
-    if (a > 0.0) {
-      l0 = unit(M[0]);
-      ph = unit(-M[1] / l0);
-    } else {
-      l0 = unit(-M[1]);
-    }
-  }
-  left[0] = l0;
-  left[1] = l1;
-  out[0] = cplx(cs, -sn);  // row 0 of the real matrix
-  out[1] = cplx(sn, cs);   // row 1
-  out[2] = ph;
-}
-
-void chain_gate(const cplx* M, bool normalize, cplx* carry, cplx* out) {
-  const cplx k[2] = {carry[0], carry[1]};
-  const double k0 = std::abs(k[0]), rho = std::abs(k[1]) / k0;
-  cplx U[4], left[2];
-  for (int r = 0; r < 2; ++r) {
-    U[2 * r] = M[2 * r] * (k[0] / k0);
-    U[2 * r + 1] = M[2 * r + 1] * (k[1] / (k0 * rho));
-  }
-  split_gate(U, left, out);
-  const double cs = out[0].real(), sn = out[1].real();
-  const cplx ph = out[2];
+// The numbers that the kernel gets are rounded to double; what it makes of the amplitudes with
+// them is known exactly.  So the carry is fitted to the rounded numbers, and in long double: each
+// row's factor is the least-squares one between the row that is wanted and the row that is
+// applied, both as they act on true amplitudes (columns divided by the old carry).  Factors formed
+// in double from the numbers before rounding leave out errors that all have one sign.
+void chain_gate(const cplx* M, bool normalize, lcplx* carry, cplx* out) {
+  typedef long double ld;
+  const lcplx m[4] = {lcplx(M[0]), lcplx(M[1]), lcplx(M[2]), lcplx(M[3])};
+  const lcplx w[4] = {m[0] * carry[0], m[1] * carry[1], m[2] * carry[0], m[3] * carry[1]};
+  // p: the phase by which both rows' second entries turn against their first (row 0: and pi)
+  const lcplx z = w[3] * std::conj(w[2]) - w[1] * std::conj(w[0]);
+  const ld az = std::abs(z);
+  const lcplx ph = az > 0 ? z / az : lcplx(1);
+  const bool cross = std::abs(w[2]) > std::abs(w[0]);
+  double re, im, r[4];
   if (normalize) {
-    out[0] = cplx(k0 * cs, -k0 * sn * rho);
-    out[1] = cplx(k0 * sn, k0 * cs * rho);
+    re = (double)ph.real();
+    im = (double)ph.imag();
+    const lcplx p(re, im);
+    lcplx u0 = cross ? -w[1] / p : w[0], u1 = cross ? w[2] : w[3] / p;
+    u0 /= std::abs(u0);
+    u1 /= std::abs(u1);
+    r[0] = (double)(w[0] * std::conj(u0)).real();
+    r[1] = (double)(w[1] / p * std::conj(u0)).real();
+    r[2] = (double)(w[2] * std::conj(u1)).real();
+    r[3] = (double)(w[3] / p * std::conj(u1)).real();
     out[3] = (double)kChainFull;
-    carry[0] = left[0];
-    carry[1] = left[1];
   } else {
-    // p keeps the larger of its two parts at 1; g: what is left for R's second column
+    // p keeps the larger of its two parts at 1, each row the larger of its entries
     const bool imag = std::abs(ph.imag()) > std::abs(ph.real());
-    const double g = rho * (imag ? ph.imag() : ph.real());
-    out[2] = imag ? cplx(ph.real() / ph.imag(), 1.0) : cplx(1.0, ph.imag() / ph.real());
-    // [[c, -s g], [s, c g]] with its larger entries at 1
-    const bool cross = sn > cs;
-    if (cross) {
-      out[0] = cplx(-cs / (sn * g), 1.0);
-      out[1] = cplx(1.0, cs * g / sn);
-      carry[0] = k0 * left[0] * (-sn * g);
-      carry[1] = k0 * left[1] * sn;
-    } else {
-      out[0] = cplx(1.0, -sn * g / cs);
-      out[1] = cplx(sn / (cs * g), 1.0);
-      carry[0] = k0 * left[0] * cs;
-      carry[1] = k0 * left[1] * (cs * g);
-    }
+    re = imag ? (double)(ph.real() / ph.imag()) : 1.0;
+    im = imag ? 1.0 : (double)(ph.imag() / ph.real());
+    const lcplx p(re, im);
+    r[0] = cross ? (double)(w[0] * p / w[1]).real() : 1.0;
+    r[1] = cross ? 1.0 : (double)(w[1] / (p * w[0])).real();
+    r[2] = cross ? 1.0 : (double)(w[2] * p / w[3]).real();
+    r[3] = cross ? (double)(w[3] / (p * w[2])).real() : 1.0;
     out[3] = (double)(kChainUnit + (imag ? kChainImag : 0) + (cross ? kChainCross : 0));
   }
+  out[0] = cplx(r[0], r[1]);
+  out[1] = cplx(r[2], r[3]);
+  out[2] = cplx(re, im);
+  const lcplx p(re, im), k0 = carry[0], k1 = carry[1];
+  for (int i = 0; i < 2; ++i) {
+    const lcplx a = (ld)r[2 * i] / k0, b = (ld)r[2 * i + 1] * p / k1;
+    carry[i] = (m[2 * i] * std::conj(a) + m[2 * i + 1] * std::conj(b)) / (std::norm(a) + std::norm(b));
+  }
+}
+
+void split_gate(const cplx* M, cplx* left, cplx* out) {
+  lcplx carry[2] = {1, 1};
+  chain_gate(M, true, carry, out);
+  for (int i = 0; i < 2; ++i) left[i] = cplx((double)carry[i].real(), (double)carry[i].imag());
 }
 
 void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const AngleOverride* ov, int n_ov,
@@ -1778,7 +1762,7 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
   // phase chains: the left diagonal each qubit carries to its next gate, and its gates since the
   // diagonal's moduli were last folded in
   std::vector<int> gates_since((size_t)c->n_qubits, 0);
-  std::vector<cplx> carry(2 * (size_t)c->n_qubits, cplx(1.0, 0.0));
+  std::vector<lcplx> carry(2 * (size_t)c->n_qubits, lcplx(1));
   for (const Fill& f : p.fills) {
     cplx* dst = out + f.offset;
     switch (f.kind) {
@@ -1786,15 +1770,18 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
         const Prim& pr = p.prims[f.prim];
         cplx M[4];
         prim_numbers(pr, c, &ang[3 * pr.gate], M);
-        cplx* cq = &carry[2 * (size_t)pr.q0];
+        lcplx* cq = &carry[2 * (size_t)pr.q0];
         int& since = gates_since[pr.q0];
         if (f.count) {
           const bool normalize = since >= kChainGates;
           chain_gate(M, normalize, cq, dst);
           since = normalize ? 0 : since + 1;
         } else {
-          for (int e = 0; e < 4; ++e) dst[e] = M[e] * cq[e & 1];
-          cq[0] = cq[1] = cplx(1.0, 0.0);
+          for (int e = 0; e < 4; ++e) {
+            const lcplx v = lcplx(M[e]) * cq[e & 1];
+            dst[e] = cplx((double)v.real(), (double)v.imag());
+          }
+          cq[0] = cq[1] = lcplx(1);
           since = 0;
         }
         break;

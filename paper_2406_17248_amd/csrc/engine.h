@@ -12,6 +12,8 @@
 namespace qsv {
 
 using cplx = std::complex<double>;
+// Diagonals carried along phase chains
+using lcplx = std::complex<long double>;
 
 // Thrown inside the library only; converted to a status code at the ABI boundary.
 struct Error {
@@ -222,17 +224,15 @@ struct PlanOptions {
 // out receives 256 reals, lane-major (lane l's four values at 4l).
 void block_operands(const cplx* M8, int dtype, double* out);
 
-// A unitary 2x2 M (row-major) as diag(left[0], left[1]) R diag(1, out[2]) with R real: out[0] =
-// (R00, R01) and out[1] = (R10, R11) as complex pairs of reals.
-void split_gate(const cplx* M, cplx* left, cplx* out);
-
 // A gate of a phase chain: unitary M (row-major) after the diagonal `carry` that its qubit
 // brings along equals diag(new carry) R diag(1, p); out[0] = (R00, R01) and out[1] = (R10,
 // R11) as complex pairs of reals, out[2] = p, out[3].x the form (kChain*).  R keeps two unit
 // entries and p a unit real or imaginary part (its modulus and R's are carried), so that
 // kernels spend one multiply-add on each of the others; the carried moduli shrink by up to a
 // half per gate.  normalize: R with its moduli, p a phase, and the new carry of modulus 1.
-void chain_gate(const cplx* M, bool normalize, cplx* carry, cplx* out);
+void chain_gate(const cplx* M, bool normalize, lcplx* carry, cplx* out);
+// The same for a gate by itself, normalized: M = diag(left[0], left[1]) R diag(1, out[2]).
+void split_gate(const cplx* M, cplx* left, cplx* out);
 // Gates between normalizing ones, so that unnormalized amplitudes (up to 2^gates larger per
 // qubit, 34 qubits) stay finite in double: 2^(15 * 34) < 2^1023.
 constexpr int kChainGates = 15;

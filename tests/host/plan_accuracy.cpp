@@ -8,7 +8,9 @@
 //          than each gate in double by itself.  Tables of their products, rounded to double, are up
 //          to 10 (states) and 60 (norms) times further off.
 //   chain  layers of general gates (U3, explicit unitaries): closer than the same gates split
-//          one by one in double, the phases between them carried in double.
+//          one by one in double, the phases between them carried in double (2 to 15 times closer;
+//          carries formed in double from the numbers before rounding are 1.0 to 1.2 times as
+//          far off).
 //
 // Argument: fixed or chain.  Exit status 0 when every family holds.
 #include <cstdio>

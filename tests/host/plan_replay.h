@@ -14,7 +14,7 @@
 
 namespace replay {
 using namespace qsv;
-typedef std::complex<long double> lcplx;
+
 
 inline double fma3(double a, double b, double c) { return std::fma(a, b, c); }
 

@@ -28,7 +28,7 @@ def test_plans_compute_their_circuits(tmp_path):
     assert res.returncode == 0, res.stdout[-3000:] + res.stderr[-3000:]
 
 
-@pytest.mark.parametrize("gates", ["fixed"])
+@pytest.mark.parametrize("gates", ["fixed", "chain"])
 def test_rounding_errors_of_plans(tmp_path, gates):
     """Layered circuits in complex128: their plans are no further off than the gates one by one
     (tests/host/plan_accuracy.cpp)."""
