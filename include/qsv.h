@@ -184,7 +184,9 @@ int qsv_state_get_option(const qsv_state* s, int32_t option, int64_t* value);
 
 /* ---- hot path ------------------------------------------------------------------------ */
 /* psi <- U(params) psi (section 2.6, apply_circuit).  n_params must cover every
- * param_index used.  The circuit's n_qubits must equal the state's. */
+ * param_index used.  The circuit's n_qubits must equal the state's.  In complex128, amplitudes of
+ * the input up to 2^(1023 - 15 n_qubits) in magnitude (2^513 at 34 qubits: any state whose norm
+ * is finite) go through without overflow. */
 int qsv_apply_circuit(qsv_state* s, const qsv_circuit* c, const double* params, size_t n_params);
 
 /* <psi|H|psi> (section 2.6, get_expectation with U_l = U_r = I); the state is unchanged.

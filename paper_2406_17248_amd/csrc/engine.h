@@ -233,8 +233,9 @@ void block_operands(const cplx* M8, int dtype, double* out);
 void chain_gate(const cplx* M, bool normalize, lcplx* carry, cplx* out);
 // The same for a gate by itself, normalized: M = diag(left[0], left[1]) R diag(1, out[2]).
 void split_gate(const cplx* M, cplx* left, cplx* out);
-// Gates between normalizing ones, so that unnormalized amplitudes (up to 2^gates larger per
-// qubit, 34 qubits) stay finite in double: 2^(15 * 34) < 2^1023.
+// Gates between normalizing ones.  In between, passes store amplitudes up to 2^gates larger per
+// qubit (general gates: 2^4 on average, 1e37 on 30 qubits), so an input state's have to stay
+// below 2^(1023 - 15 n): 2^513 on 34 qubits, which every state of finite norm does.
 constexpr int kChainGates = 15;
 
 // Default tile widths of forward and adjoint plans, measured on the 30-qubit brick circuit

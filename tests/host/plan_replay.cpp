@@ -3,7 +3,8 @@
 // (plan_replay.h) on a random state, and the result is compared with the circuit gate by gate in
 // long double: forward plans of both amplitude types (the records of one serve the other's
 // arithmetic, done here in double), with and without relayout, for launches of few and of many
-// tiles; reverse sweeps with their gradients.  Exit status 0 when every check holds.
+// tiles; reverse sweeps with their gradients.  States of the largest amplitudes go through chains
+// like small ones.  Exit status 0 when every check holds.
 #include <cstdio>
 #include <random>
 
@@ -136,6 +137,7 @@ double distance(const std::vector<cplx>& x, const std::vector<lcplx>& y) {
 
 long g_plans = 0, g_flips = 0, g_phases = 0, g_chains = 0, g_blocks = 0, g_remaps = 0, g_half = 0, g_one = 0, g_grads = 0;
 int g_bad = 0;
+double g_largest = 0.0;
 
 void count(const Plan& p, const Machine& m) {
   ++g_plans;
@@ -254,6 +256,48 @@ void check_reverse(const Circ& k, int n, const std::vector<double>& params, std:
   }
 }
 
+// Chains store amplitudes up to 2^(kChainGates n) times their size: a state of the largest
+// amplitudes that leave room for it comes out as its small copy does, bit for bit.
+void check_scale() {
+  const int n = 10;
+  std::mt19937_64 rng(5);
+  for (int kind = 0; kind < 2; ++kind) {
+    Circ k;
+    for (int l = 0; l < 50; ++l) {
+      for (int q = 0; q < n; ++q) {
+        qsv_gate g = blank(kind ? QSV_GATE_MAT1 : QSV_GATE_U3, q);
+        if (kind) {
+          push_unitary(k, g, 2, rng);
+        } else {
+          g.angle_const[0] = M_PI / 2;
+          g.angle_const[2] = M_PI / 4;
+        }
+        k.gates.push_back(g);
+      }
+      for (int a = l % 2; a + 1 < n; a += 2) {
+        qsv_gate g = blank(QSV_GATE_Z, a + 1);
+        g.ctrl_mask = 1ull << a;
+        k.gates.push_back(g);
+      }
+    }
+    k.finish(n);
+    const Plan p = build_plan(&k.c, false, state_plan_options(QSV_C128, n, 9, 9, false, true, false));
+    const std::vector<cplx> psi = random_state(n, rng);  // (amplitudes below 1)
+    std::vector<cplx> big = psi;
+    const double up = std::ldexp(1.0, 1023 - kChainGates * n - 1);
+    for (cplx& z : big) z *= up;
+    const Machine small(p, &k.c, {}, psi), large(p, &k.c, {}, big);
+    if (!(small.largest <= std::ldexp(1.0, kChainGates * n))) {
+      printf("stored amplitudes up to %.2e\n", small.largest);
+      g_bad = 1;
+    }
+    for (size_t i = 0; i < psi.size(); ++i)
+      if (large.v[i] != small.v[i] * up) g_bad = 1;
+    if (g_bad) printf("scaled state, kind %d\n", kind);
+    if (kind == 0) g_largest = small.largest;
+  }
+}
+
 }  // namespace
 
 int main() {
@@ -275,13 +319,14 @@ int main() {
         check_reverse(r, n, params, rng, "random");
       }
     }
+    check_scale();
   } catch (const Error& e) {
     printf("planner error %d: %s\n", e.status, e.msg.c_str());
     return 2;
   }
   printf("plans replayed %ld (gradients %ld): flips %ld, phase runs %ld, chain gates %ld, blocks %ld, remaps %ld, "
-         "passes with halved remaps %ld, with single phases %ld\n",
-         g_plans, g_grads, g_flips, g_phases, g_chains, g_blocks, g_remaps, g_half, g_one);
+         "passes with halved remaps %ld, with single phases %ld; stored amplitudes up to %.1e\n",
+         g_plans, g_grads, g_flips, g_phases, g_chains, g_blocks, g_remaps, g_half, g_one, g_largest);
   return g_bad || g_plans < 300 || g_flips < 1000 || g_phases < 1000 || g_chains < 500 || g_blocks < 100 ||
          g_remaps < 500 || g_half < 20 || g_one < 20;
 }
