@@ -1991,8 +1991,10 @@ void pauli_multi_tables(const std::vector<PauliGroup>& groups, const PauliLaunch
     PauliMultiGroup M{};
     M.x = L.kind == PL_TILE ? local(P.xmask) : P.xmask;
     M.first = (int32_t)mt.size();
-    // the highest bit of x, where whole waves or slots share it
-    if (!lambda && M.x >> 6) M.half = 1ull << (63 - __builtin_clzll(M.x));
+    // the highest bit of x, where whole waves or slots share it and twice the coefficients is finite
+    double sum = 0.0;
+    for (size_t k = 0; k < P.zmasks.size(); ++k) sum += std::abs(P.cre[k]) + std::abs(P.cim[k]);
+    if (!lambda && M.x >> 6 && std::isfinite(2.0 * sum)) M.half = 1ull << (63 - __builtin_clzll(M.x));
     for (int im = 0; im < 2; ++im)
       for (size_t k = 0; k < P.zmasks.size(); ++k) {
         // i^{popcount(x & z)}: even counts real, odd ones imaginary (whatever the coefficient)

@@ -1,7 +1,9 @@
 // Host checks of Pauli-sum plans at their limits (no GPU).  Argument:
 //   plan  planning many groups takes less host time than one pass over the state per group would
 //         at the rate of a large copy.
+//   coefficients  of the largest size stay finite in the tables of expectations.
 // Exit status 0 when the check holds.
+#include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <ctime>
@@ -40,8 +42,37 @@ static int check_plan() {
   return bad;
 }
 
+static int check_coefficients() {
+  int bad = 0;
+  for (int n : {9, 20, 24})
+    for (double c : {0.5, 8.9e307, 1.7e308}) {
+      // two x masks; on the higher one, one term or two that sum up to within the range
+      const uint64_t x[3] = {1, 1ull << (n - 1), 1ull << (n - 1)}, z[3] = {0, 0, 6};
+      const double co[3] = {1.0, c, 0.25 * c};
+      const qsv_pauli_sum h{c < 1e308 ? 3u : 2u, co, x, z};
+      const auto groups = group_pauli_sum(&h);
+      for (const PauliLaunch& L : plan_pauli(groups, n, QSV_C128, false)) {
+        if (L.kind == PL_GROUP) continue;
+        std::vector<PauliMultiGroup> mg;
+        std::vector<PauliMultiTerm> mt;
+        pauli_multi_tables(groups, L, n, false, mg, mt);
+        for (const PauliMultiGroup& g : mg) {
+          double f = 0.0;
+          for (int e = 0; e < g.n_re + g.n_im; ++e) f += mt[g.first + e].c;
+          if (!std::isfinite(f)) {
+            printf("n=%d c=%g: factor %g\n", n, c, f);
+            bad = 1;
+          }
+          if (c == 0.5 && g.x >> 6 && !g.half) bad = 1;  // ordinary sums keep their half passes
+        }
+      }
+    }
+  return bad;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "plan")) return check_plan();
+  if (!strcmp(what, "coefficients")) return check_coefficients();
   return 2;
 }
