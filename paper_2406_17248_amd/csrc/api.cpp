@@ -445,9 +445,9 @@ DevPauli upload_pauli(qsv_state* s, const qsv_pauli_sum* h, DevBuf& buf, bool la
 }
 
 // Workgroups per launch (the partial columns' length) of a planned Pauli sum.
-unsigned pauli_grid(const std::vector<PauliLaunch>& launches, int n) {
+unsigned pauli_grid(const std::vector<PauliLaunch>& launches, int n, size_t batch, bool lambda) {
   for (const PauliLaunch& L : launches)
-    if (L.kind != PL_GROUP) return std::max(pauli_blocks(n), pauli_multi_blocks(n));
+    if (L.kind != PL_GROUP) return std::max(pauli_blocks(n), pauli_multi_blocks(n, batch, lambda));
   return pauli_blocks(n);
 }
 
@@ -460,7 +460,7 @@ unsigned pauli_grid(const std::vector<PauliLaunch>& launches, int n) {
 void run_pauli(qsv_state* s, const DevPauli& dp, const void* psi, void* lam, int64_t bstride, int batch,
                double* out_cols, double* partials = nullptr, int chunk = 0, bool untimed = false) {
   const int NL = (int)dp.launches.size();
-  const unsigned nblk = pauli_grid(dp.launches, s->n);
+  const unsigned nblk = pauli_grid(dp.launches, s->n, (size_t)batch, lam != nullptr);
   if (!partials) {
     const size_t need = (size_t)batch * 2 * NL * nblk * sizeof(double);
     s->partials.reserve(need ? need : 8);
@@ -887,7 +887,7 @@ int qsv_expectation_noalloc(qsv_state* s, const qsv_pauli_sum* h, double* out_re
       const size_t tab = pauli_table_bytes(groups, launches, s->n, 8);
       const size_t out_off = align_up(tab, 256);
       const size_t part_off = align_up(out_off + (size_t)2 * G * sizeof(double), 256);
-      const size_t part_bytes = (size_t)2 * kNoallocChunk * pauli_grid(launches, s->n) * sizeof(double);
+      const size_t part_bytes = (size_t)2 * kNoallocChunk * pauli_grid(launches, s->n, 1, false) * sizeof(double);
       if (part_off + part_bytes > kNoallocScratchBytes) fail(QSV_ERANGE, "Pauli sum too large for the fixed scratch");
       std::vector<char> host(tab);
       DevPauli dp = pack_pauli(std::move(groups), std::move(launches), s->n, false, host.data(), scr, 8);

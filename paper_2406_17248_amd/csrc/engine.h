@@ -308,6 +308,8 @@ struct PauliLaunch {
 };
 // Every group in exactly one launch.  in_order: the groups add to H psi in their order.
 std::vector<PauliLaunch> plan_pauli(const std::vector<PauliGroup>& groups, int32_t n, int32_t dtype, bool in_order);
+// Workgroups per batch item of a launch of several groups.
+unsigned pauli_multi_blocks(int32_t n, size_t batch, bool lambda);
 // The group and term records of a PL_GATHER / PL_TILE launch; lambda: H psi is written.
 void pauli_multi_tables(const std::vector<PauliGroup>& groups, const PauliLaunch& L, int32_t n, bool lambda,
                         std::vector<PauliMultiGroup>& mg, std::vector<PauliMultiTerm>& mt);

@@ -243,13 +243,6 @@ __global__ __launch_bounds__(NT) void pauli_tile(PauliMultiArgs A) {
 }
 
 // ------------------------------------------------------------------------------------------
-unsigned pauli_multi_blocks(int n) {
-  const uint64_t b = ((1ull << n) + 255) / 256;
-  // few chunks: room for the groups of each to spread over several workgroups
-  if (b < 128) return (unsigned)(b * (128 / b));
-  return (unsigned)(b < 2048 ? b : 2048);
-}
-
 template <typename R>
 static void gather(PauliMultiArgs A, dim3 grid, hipStream_t s) {
   const uint64_t chunks = ((1ull << A.n_qubits) + 255) / 256;

@@ -40,7 +40,6 @@ hipError_t launch_diag(int dtype, void* psi, int64_t bstride, int batch, int n, 
 unsigned pauli_blocks(int n);
 hipError_t launch_pauli_group(int dtype, const PauliGroupArgs& A, unsigned blocks, int batch, hipStream_t s);
 // Passes over several groups; `blocks` workgroups (the partial columns' length).
-unsigned pauli_multi_blocks(int n);
 hipError_t launch_pauli_gather(int dtype, const PauliMultiArgs& A, unsigned blocks, int batch, hipStream_t s);
 hipError_t launch_pauli_tile(int dtype, const PauliMultiArgs& A, unsigned blocks, int batch, hipStream_t s);
 hipError_t launch_reduce_columns(const double* in, int64_t len, int64_t ncols, double* out, hipStream_t s);

@@ -1,6 +1,8 @@
 // Host checks of Pauli-sum plans at their limits (no GPU).  Argument:
 //   plan  planning many groups takes less host time than one pass over the state per group would
 //         at the rate of a large copy.
+//   grid  launches over batches start no workgroups beyond a batch item's chunks of 256 outputs,
+//         expectations of few chunks in all up to 128 that share them.
 //   coefficients  of the largest size stay finite in the tables of expectations.
 // Exit status 0 when the check holds.
 #include <cmath>
@@ -70,9 +72,27 @@ static int check_coefficients() {
   return bad;
 }
 
+static int check_grid() {
+  int bad = 0;
+  for (int n = 1; n <= 34; ++n)
+    for (size_t batch : {1, 2, 3, 100, 127, 128, 5000, 65535})
+      for (bool lambda : {false, true}) {
+        const uint64_t chunks = ((1ull << n) + 255) / 256, b = pauli_multi_blocks(n, batch, lambda);
+        const bool shared = !lambda && chunks * batch < 128;
+        // whole workgroups per chunk, all of them with work, enough of them
+        if (b < 1 || b > 2048 || (b > chunks && (!shared || b % chunks || b * batch > 128)) ||
+            (shared && 2 * b * batch <= 128) || (!shared && b != std::min<uint64_t>(chunks, 2048))) {
+          printf("n=%d batch=%zu lambda=%d: %zu workgroups\n", n, batch, (int)lambda, (size_t)b);
+          bad = 1;
+        }
+      }
+  return bad;
+}
+
 int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "plan")) return check_plan();
   if (!strcmp(what, "coefficients")) return check_coefficients();
+  if (!strcmp(what, "grid")) return check_grid();
   return 2;
 }
