@@ -1581,6 +1581,23 @@ Plan build_plan(const qsv_circuit* c, bool adjoint, const PlanOptions& opt) {
     }
     plan.passes.push_back(dp);
   }
+  // A layer's gates often share their angle (QAOA mixers), and their sines and cosines are most of
+  // the work of binding a batch (16 qubits, 6 layers: 14 -> 6 us a row for the reverse sweep):
+  // gates that may have the numbers of the gate before are marked here, so that binding others
+  // costs nothing more.
+  const Fill* last = nullptr;
+  for (Fill& f : plan.fills) {
+    if (f.kind != F_PRIM_MATRIX) continue;
+    const Prim& a = plan.prims[f.prim];
+    if (last && a.recipe == M_GATE) {
+      const Prim& b = plan.prims[last->prim];
+      const qsv_gate &g = c->gates[a.gate], &h = c->gates[b.gate];
+      if (b.recipe == M_GATE && g.kind == h.kind && kNAngles[g.kind] == 1 && a.dagger == b.dagger &&
+          g.param_index[0] == h.param_index[0])
+        f.count = prim_size(a);
+    }
+    last = &f;
+  }
   return plan;
 }
 
@@ -1736,33 +1753,14 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
   std::vector<double> ang(3 * c->n_gates);
   for (size_t i = 0; i < c->n_gates; ++i) gate_angles(c->gates[i], params, &ang[3 * i]);
   for (int k = 0; k < n_ov; ++k) ang[3 * ov[k].gate + ov[k].slot] = ov[k].angle;
-  // The last one-angle gate's numbers: a layer's gates often share their angle (QAOA mixers), and
-  // their sines and cosines are most of the work of binding a batch (16 qubits, 6 layers: 14 -> 6 us
-  // a row for the reverse sweep).
-  struct {
-    int kind = -1, dagger = 0, count = 0;
-    double angle = 0.0;
-    cplx v[16];
-  } last;
-  auto numbers = [&](const Prim& pr, cplx* dst) {
-    const int kind = pr.recipe == M_GATE ? c->gates[pr.gate].kind : -1;
-    if (kind < 0 || kNAngles[kind] != 1) {
-      prim_numbers(pr, c, &ang[3 * pr.gate], dst);
-      return;
-    }
-    const double a = ang[3 * pr.gate];
-    if (last.kind != kind || last.dagger != (int)pr.dagger || last.angle != a) {
-      last.kind = kind;
-      last.dagger = pr.dagger;
-      last.angle = a;
-      last.count = prim_numbers(pr, c, &ang[3 * pr.gate], last.v);
-    }
-    std::copy(last.v, last.v + last.count, dst);
+  const Fill* last = nullptr;  // the F_PRIM_MATRIX before
+  // phase chains (complex128): the left diagonal each qubit carries to its next gate, and its
+  // gates since the diagonal's moduli were last folded in
+  struct Carry {
+    lcplx d[2] = {1, 1};
+    int gates = 0;
   };
-  // phase chains: the left diagonal each qubit carries to its next gate, and its gates since the
-  // diagonal's moduli were last folded in
-  std::vector<int> gates_since((size_t)c->n_qubits, 0);
-  std::vector<lcplx> carry(2 * (size_t)c->n_qubits, lcplx(1));
+  std::vector<Carry> carry;
   for (const Fill& f : p.fills) {
     cplx* dst = out + f.offset;
     switch (f.kind) {
@@ -1770,24 +1768,27 @@ void bind_ctab(const Plan& p, const qsv_circuit* c, const double* params, const 
         const Prim& pr = p.prims[f.prim];
         cplx M[4];
         prim_numbers(pr, c, &ang[3 * pr.gate], M);
-        lcplx* cq = &carry[2 * (size_t)pr.q0];
-        int& since = gates_since[pr.q0];
+        if (carry.empty()) carry.resize((size_t)c->n_qubits);
+        Carry& q = carry[pr.q0];
         if (f.count) {
-          const bool normalize = since >= kChainGates;
-          chain_gate(M, normalize, cq, dst);
-          since = normalize ? 0 : since + 1;
+          const bool normalize = q.gates >= kChainGates;
+          chain_gate(M, normalize, q.d, dst);
+          q.gates = normalize ? 0 : q.gates + 1;
         } else {
           for (int e = 0; e < 4; ++e) {
-            const lcplx v = lcplx(M[e]) * cq[e & 1];
+            const lcplx v = lcplx(M[e]) * q.d[e & 1];
             dst[e] = cplx((double)v.real(), (double)v.imag());
           }
-          cq[0] = cq[1] = lcplx(1);
-          since = 0;
+          q = Carry();
         }
         break;
       }
       case F_PRIM_MATRIX: {
-        numbers(p.prims[f.prim], dst);
+        const Prim& pr = p.prims[f.prim];
+        const double* a = &ang[3 * pr.gate];
+        if (f.count && a[0] == ang[3 * p.prims[last->prim].gate]) std::copy(out + last->offset, out + last->offset + f.count, dst);
+        else prim_numbers(pr, c, a, dst);
+        last = &f;
         break;
       }
       case F_PRIM_GEN:

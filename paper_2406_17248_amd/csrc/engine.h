@@ -66,7 +66,9 @@ struct Pass {
 
 // Where a ctab entry block comes from at bind time.
 enum FillKind : int32_t {
-  F_PRIM_MATRIX = 0,  // the primitive's matrix: 4 (dense1), 16 (dense2), 2 or 4 (diag) entries
+  F_PRIM_MATRIX = 0,  // the primitive's matrix: 4 (dense1), 16 (dense2), 2 or 4 (diag) entries;
+                      // count > 0: so many entries, those of the F_PRIM_MATRIX before it if the
+                      // two gates' angles are equal
   F_PRIM_GEN,         // coeff * generator of the primitive: same sizes (diag: real weights)
   F_ZZ_PHASES,        // exp(-+ i theta/2 (E - 2c)), c = 0..E (sign by dagger)
   F_ZZ_GEN,           // coeff * (E - 2c) as real weights

@@ -298,6 +298,43 @@ void check_scale() {
   }
 }
 
+// Numbers that neighbours share are looked up only where gates may share their angle: layers of RX
+// with one parameter, equal or shifted angles, against RY and RZ with parameters of their own.
+void check_shared() {
+  const int n = 9;
+  std::mt19937_64 rng(8);
+  for (int kind = 0; kind < 3; ++kind) {
+    Circ k;
+    const int layers = 3;
+    for (int l = 0; l < layers; ++l) {
+      for (int q = 0; q < n; ++q) {
+        qsv_gate g = blank(kind < 2 ? QSV_GATE_RX : q % 2 ? QSV_GATE_RY : QSV_GATE_RX, q);
+        g.param_index[0] = kind < 2 ? l : n * l + q;
+        g.param_coeff[0] = 1.0;
+        if (kind == 1) g.angle_const[0] = 0.25 * (q / 3);
+        k.gates.push_back(g);
+      }
+      qsv_gate z = blank(QSV_GATE_Z, 0);
+      z.ctrl_mask = 2;
+      k.gates.push_back(z);
+    }
+    k.finish(n);
+    std::vector<double> params(n * layers);
+    for (double& v : params) v = std::uniform_real_distribution<double>(-3.0, 3.0)(rng);
+    int marked = 0;
+    for (bool adjoint : {false, true}) {
+      const Plan p = build_plan(&k.c, adjoint, state_plan_options(QSV_C128, n, 9, 9, adjoint, true, false));
+      for (const Fill& f : p.fills) marked += f.kind == F_PRIM_MATRIX && f.count > 0;
+    }
+    if (kind < 2 ? marked < layers * (n - 1) : marked != 0) {
+      printf("layers of kind %d: %d gates look for their neighbour's numbers\n", kind, marked);
+      g_bad = 1;
+    }
+    check_forward(k, n, params, rng, "shared angles");
+    check_reverse(k, n, params, rng, "shared angles");
+  }
+}
+
 }  // namespace
 
 int main() {
@@ -320,6 +357,7 @@ int main() {
       }
     }
     check_scale();
+    check_shared();
   } catch (const Error& e) {
     printf("planner error %d: %s\n", e.status, e.msg.c_str());
     return 2;
