@@ -1971,6 +1971,10 @@ std::vector<PauliLaunch> plan_pauli(const std::vector<PauliGroup>& groups, int32
     else out.push_back(std::move(L));
   }
   for (int32_t g : single) alone(g);
+  // no tile: the groups in their order (a large diagonal group that comes first writes H psi faster
+  // than it adds to it: 276 ZZ terms and one X on 24 qubits, complex64, H psi 187 -> 175 us)
+  if (std::all_of(out.begin(), out.end(), [](const PauliLaunch& L) { return L.kind == PL_GROUP; }))
+    std::sort(out.begin(), out.end(), [](const PauliLaunch& a, const PauliLaunch& b) { return a.groups[0] < b.groups[0]; });
   return out;
 }
 

@@ -3,6 +3,7 @@
 //         at the rate of a large copy.
 //   grid  launches over batches start no workgroups beyond a batch item's chunks of 256 outputs,
 //         expectations of few chunks in all up to 128 that share them.
+//   order  plans without tiles keep the groups' order.
 //   coefficients  of the largest size stay finite in the tables of expectations.
 // Exit status 0 when the check holds.
 #include <cmath>
@@ -72,6 +73,38 @@ static int check_coefficients() {
   return bad;
 }
 
+static int check_order() {
+  std::mt19937_64 rng(9);
+  int bad = 0;
+  for (int n : {23, 24, 28})
+    for (int first : {0, 1}) {
+      // all pairs of Z (one diagonal group) with one X, or with strings too wide for a tile
+      for (int wide : {0, 5}) {
+        std::vector<uint64_t> x, z;
+        for (int a = 0; a < n; ++a)
+          for (int b = 0; b < a; ++b) {
+            x.push_back(0);
+            z.push_back(1ull << a | 1ull << b);
+          }
+        std::vector<uint64_t> mx{1ull << (n - 1)};
+        if (wide) mx.clear();
+        for (int k = 0; k < wide; ++k) mx.push_back(((1ull << n) - 1) & ~(1ull << k));
+        for (uint64_t m : mx) {
+          x.insert(first ? x.begin() : x.end(), m);
+          z.insert(first ? z.begin() : z.end(), 0);
+        }
+        const std::vector<double> c(x.size(), 0.5);
+        const qsv_pauli_sum h{x.size(), c.data(), x.data(), z.data()};
+        const auto groups = group_pauli_sum(&h);
+        const auto plan = plan_pauli(groups, n, n == 23 ? QSV_C128 : QSV_C64, false);
+        if (plan.size() != groups.size()) bad = 1;
+        for (size_t i = 0; i < plan.size(); ++i)
+          if (plan[i].kind != PL_GROUP || plan[i].groups[0] != (int32_t)i) bad = 1;
+      }
+    }
+  return bad;
+}
+
 static int check_grid() {
   int bad = 0;
   for (int n = 1; n <= 34; ++n)
@@ -93,6 +126,7 @@ int main(int argc, char** argv) {
   const char* what = argc > 1 ? argv[1] : "";
   if (!strcmp(what, "plan")) return check_plan();
   if (!strcmp(what, "coefficients")) return check_coefficients();
+  if (!strcmp(what, "order")) return check_order();
   if (!strcmp(what, "grid")) return check_grid();
   return 2;
 }

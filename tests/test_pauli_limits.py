@@ -20,7 +20,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["plan", "coefficients", "grid"])
+@pytest.mark.parametrize("what", ["plan", "coefficients", "grid", "order"])
 def test_limits(program, what):
     res = subprocess.run([program, what], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
