@@ -479,7 +479,7 @@ template <typename R> constexpr int kSplitWaves = sizeof(R) == 4 ? 6 : 7;
 // 79 in complex64, five waves per SIMD instead of six: 2.4 %).  10-qubit ansatz gradient 230 ->
 // 195 us, 48 uneven ansatz circuits 2570 -> 2200 us; a 20-qubit one 1830 -> 1510 us.
 // ALT: SPLIT in forward passes, ONE in reverse sweeps.
-template <typename R, int RB, int MAXM, bool ADJ, bool FULL, bool ALT>
+template <typename R, int RB, int MAXM, bool ADJ, bool FULL, bool ALT, bool WARM>
 __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, const int b) {
   using C = typename CT<R>::T;
   static_assert(RB == 3 || RB == 4, "register blocks of three or four bits");
@@ -554,13 +554,15 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
   // load per 128-byte line brings all of them into this XCD's L2 at once, while the tile
   // loads.  10-qubit, 80-parameter ansatz (one workgroup, 116 ops): 500 -> 370 us per energy
   // and gradient.  Launches of many tiles share the lines, and the loads only cost there
-  // (27-qubit brick 14.77 -> 14.93 ms), so they leave it out (kWarmTiles).
+  // (27-qubit brick 14.77 -> 14.93 ms), so they leave it out (kWarmTiles): by A.warm, or with the
+  // code itself (WARM false) where its registers alone cost (complex64 reverse sweeps without
+  // runs of phases, 64 sets of the 24-qubit QAOA: 189.2 -> 185.6 ms).
   uint32_t warm = 0;
   auto touch = [&](const void* p, int64_t bytes) {
     for (int64_t o = (int64_t)tid * 128; o < bytes; o += (int64_t)NT * 128)
       warm ^= *reinterpret_cast<const uint32_t*>(static_cast<const char*>(p) + o);
   };
-  if (A.warm) {
+  if (WARM && A.warm) {
     touch(A.ops, (int64_t)A.n_ops * sizeof(TileOp));
     touch(T + A.ctab_lo, (int64_t)A.ctab_n * sizeof(C));
     touch(A.diag + A.diag_lo, (int64_t)A.diag_n * sizeof(DiagEntry));
@@ -1057,14 +1059,14 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
   }
 }
 
-template <typename R, int RB, int MAXM, bool ADJ, bool ALT>
+template <typename R, int RB, int MAXM, bool ADJ, bool ALT, bool WARM>
 __global__ __launch_bounds__(1 << (MAXM - RB), ALT && !ADJ ? kSplitWaves<R> : 1) void tile_pass_rb(PassArgs A) {
   // Workgroups go to the 8 XCDs in turn; give each XCD a contiguous range of tiles, so
   // tiles that share cache lines (they differ only in low qubits outside the tile) run
   // back to back behind the same L2.
   const uint32_t g = gridDim.x, w = blockIdx.x;
   const uint64_t t = (g % 8 == 0) ? (uint64_t)(w & 7) * (g >> 3) + (w >> 3) : w;
-  rb_body<R, RB, MAXM, ADJ, true, ALT>(A, t, blockIdx.y);
+  rb_body<R, RB, MAXM, ADJ, true, ALT, WARM>(A, t, blockIdx.y);
 }
 
 // Many circuits in one launch: item i owns workgroups [prefix[i], prefix[i+1]); each
@@ -1079,7 +1081,7 @@ __global__ __launch_bounds__(1 << (MAXM - RB)) void tile_pass_rb_multi(const Pas
     if (ld(prefix + mid) <= w) lo = mid; else hi = mid;
   }
   const PassArgs A = items[lo];
-  rb_body<R, RB, MAXM, ADJ, false, ADJ>(A, (uint64_t)(w - ld(prefix + lo)), 0);
+  rb_body<R, RB, MAXM, ADJ, false, ADJ, true>(A, (uint64_t)(w - ld(prefix + lo)), 0);
 }
 
 template <typename R, int RB, int MAXM, bool ADJ>
@@ -1088,8 +1090,10 @@ static hipError_t rb_launch_one(const PassArgs& A, dim3 grid, hipStream_t s) {
   // four register bits: complex64 forward passes only (their registers allow 4 waves/SIMD)
   if constexpr (bytes <= 131072 && (RB == 3 || (!ADJ && sizeof(R) == 4 && MAXM >= 10))) {
     const size_t dyn = rb_dyn_lds<R>(MAXM, ADJ, A.win_n, A.pass_pslots);
-    if (A.alt) tile_pass_rb<R, RB, MAXM, ADJ, true><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
-    else tile_pass_rb<R, RB, MAXM, ADJ, false><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
+    constexpr bool lean = ADJ && sizeof(R) == 4;  // (see WARM)
+    if (A.alt) tile_pass_rb<R, RB, MAXM, ADJ, true, true><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
+    else if (lean && !A.warm) tile_pass_rb<R, RB, MAXM, ADJ, false, !lean><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
+    else tile_pass_rb<R, RB, MAXM, ADJ, false, true><<<grid, 1 << (MAXM - RB), dyn, s>>>(A);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
