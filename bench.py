@@ -40,7 +40,9 @@ FLOP_PER_AMP_DENSE1 = 14
 METRIC = "state-vector HBM GB/s vs peak; adjoint grad evals/s vs parameter-shift"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "tile_pass_brick30_traffic.txt")
 QAOA_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "tile_pass_adjoint_qaoa24_traffic.txt")
-TRAFFIC_SOURCES = ["tile_rb.h", "qsv_kernels.hip", "engine.cpp", "api.cpp"]
+# What the profiled passes are made of: kernels with every header they include, planner, launches.
+TRAFFIC_SOURCES = ["tile_rb.hip", "tile_rb.h", "device_util.h", "qsv_ops.h", "qsv_kernels.h", "qsv_kernels.hip",
+                   "engine.h", "engine.cpp", "api.cpp"]
 
 
 def sources_digest():
