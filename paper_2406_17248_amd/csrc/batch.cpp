@@ -257,7 +257,7 @@ void build(qsv_batch* b) {
         A.lay0_thr = dp.lay0_thr;
         A.win_lo = dp.win_lo;
         A.win_n = dp.win_n;
-        set_table_parts(A, dp, 1);
+        set_table_parts(A, dp, 1);  // (few workgroups share a circuit's tables: see kWarmTiles)
         A.pass_pslots = adjoint ? dp.pslot_count : 0;
         A.n_tiles = 1ll << (b->circ[i].n - dp.m);
         A.n_pslots = adjoint ? p.n_pslots : 0;

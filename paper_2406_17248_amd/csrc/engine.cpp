@@ -1875,13 +1875,17 @@ namespace {
 
 // Diagonal groups of more terms than this run by themselves where their pattern pass applies
 // (n >= 12): it costs a term a few operations per 4096 amplitudes, a pass over several groups
-// a few per amplitude.
+// a few per amplitude, but saves a pass.  ZZ terms and X on every qubit, microseconds merged / by
+// themselves, 24 qubits: complex64 12 terms 261 / 260 (expectation), 316 / 360 (H psi), 20 277 /
+// 262, 334 / 359, 33 304 / 262, 360 / 364; complex128 20 300 / 299, 526 / 659, 33 326 / 303, 550 /
+// 662; 19 qubits, complex64, 20 39 / 42, 33 41 / 43, 50 44 / 44, 78 49 / 47.
 constexpr size_t kMergedDiagTerms = 32;
 // From this many qubits on (complex64, complex128: states of 128 MiB), tiles through LDS; below
 // it one gathering launch, whose partners the caches hold.  Microseconds per call, tiles against
 // gathering: 50 random 1-4-local terms, complex128, expectation 22 qubits 164 / 140, 23 257 /
 // 309, 25 814 / 1445, H psi 22 227 / 172, 23 372 / 430, 25 1724 / 2487; complex64, expectation
-// 23 267 / 230, 24 407 / 394, 25 730 / 823, H psi 23 310 / 274, 24 513 / 573, 25 1022 / 1137.
+// 23 267 / 230, 24 407 / 394, 25 730 / 823, H psi 23 310 / 274, 24 513 / 573, 25 1022 / 1137 (one
+// line for both uses: complex64 expectations on 24 qubits lose 3 %, H psi there gains 12).
 constexpr int kPauliTileMin[2] = {24, 23};
 // Tiles are grown from up to 8 of the groups left, the largest kept, once at most 256 are left.  Sums
 // of 50 random 1-4-local terms on 24 qubits: 1 seed 4.71 launches and 6 us of host time a sum, 8

@@ -280,9 +280,11 @@ struct PauliMultiArgs {
 };
 // pauli_tile: tile qubits and thread bits (eight slots per thread; 32 and 64 KiB of LDS for
 // complex64 and complex128).  pauli_gather: four outputs per thread from kPauliGatherFour
-// qubits on, one below.
+// qubits on, one below, where more workgroups are worth more than a term's work shared by four.  50
+// random terms, expectation in microseconds, one / four: 17 qubits 40 / 46, 18 42 / 45, 19 54 / 48,
+// 20 70 / 54 (complex64; complex128 alike; H psi 18 41 / 48, 19 51 / 50, 20 66 / 57).
 constexpr int kPauliTileQubits = 12;
 constexpr int kPauliTileThreadBits = 9;
-constexpr int kPauliGatherFour = 18;
+constexpr int kPauliGatherFour = 19;
 
 }  // namespace qsv

@@ -476,8 +476,7 @@ template <typename R> constexpr int kSplitWaves = sizeof(R) == 4 ? 6 : 7;
 
 // ONE (reverse sweeps with runs of a single uncontrolled one-qubit phase, as ansatz circuits have
 // them): those runs' straight lines, which QAOA sweeps would pay for in registers (92 instead of
-// 79 in complex64, five waves per SIMD instead of six: 2.4 %).  10-qubit ansatz gradient 230 ->
-// 195 us, 48 uneven ansatz circuits 2570 -> 2200 us; a 20-qubit one 1830 -> 1510 us.
+// 79 in complex64, five waves per SIMD instead of six: 2.4 %).
 // ALT: SPLIT in forward passes, ONE in reverse sweeps.
 template <typename R, int RB, int MAXM, bool ADJ, bool FULL, bool ALT, bool WARM>
 __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, const int b) {
@@ -807,46 +806,46 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
         }
         reg1_dispatch<RB, ADJ>(ld(&O->a), v, w, jt, reg_cur, lmask, U, grad, ADJ ? gkind : 0, G, acc);
       } else if (!SPLIT && on && type == OP_DENSE2) {
-       if constexpr (!SPLIT) {
-        // two-qubit dense gate on local bits a, b, applied to the tile staged in LDS (no
-        // gradient: parameterized two-qubit rotations are lowered to RZZ with basis changes)
-        const int a = ld(&O->a), bb = ld(&O->b);
-        const int lo = a < bb ? a : bb, hi = a < bb ? bb : a;
-        const uint32_t lm = lmask;
-        int uo[NR];
-        slot_offsets(units_cur, uo);
-        auto apply_staged = [&](C (&reg)[NR]) {
-          if (active) {
+        if constexpr (!SPLIT) {
+          // two-qubit dense gate on local bits a, b, applied to the tile staged in LDS (no
+          // gradient: parameterized two-qubit rotations are lowered to RZZ with basis changes)
+          const int a = ld(&O->a), bb = ld(&O->b);
+          const int lo = a < bb ? a : bb, hi = a < bb ? bb : a;
+          const uint32_t lm = lmask;
+          int uo[NR];
+          slot_offsets(units_cur, uo);
+          auto apply_staged = [&](C (&reg)[NR]) {
+            if (active) {
 #pragma unroll
-            for (int k = 0; k < NR; ++k) lds_at(sw_cur ^ uo[k]) = reg[k];
-          }
-          __syncthreads();
-          for (int p = tid; p < (nloc >> 2); p += NT) {
-            const int t = insert_zero(insert_zero(p, lo), hi);
-            if (((uint32_t)t & lm) != lm) continue;
-            const int idx[4] = {t, t | (1 << a), t | (1 << bb), t | (1 << a) | (1 << bb)};
-            C x[4], y[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) x[r] = buf[swz<S>(idx[r])];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              y[r] = cdot2(ldc(T + mat + 4 * r), x[0], ldc(T + mat + 4 * r + 1), x[1]);
-              y[r] = cdot2(C{1, 0}, y[r], ldc(T + mat + 4 * r + 2), x[2]);
-              y[r] = cdot2(C{1, 0}, y[r], ldc(T + mat + 4 * r + 3), x[3]);
+              for (int k = 0; k < NR; ++k) lds_at(sw_cur ^ uo[k]) = reg[k];
             }
+            __syncthreads();
+            for (int p = tid; p < (nloc >> 2); p += NT) {
+              const int t = insert_zero(insert_zero(p, lo), hi);
+              if (((uint32_t)t & lm) != lm) continue;
+              const int idx[4] = {t, t | (1 << a), t | (1 << bb), t | (1 << a) | (1 << bb)};
+              C x[4], y[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) buf[swz<S>(idx[r])] = y[r];
-          }
-          __syncthreads();
-          if (active) {
+              for (int r = 0; r < 4; ++r) x[r] = buf[swz<S>(idx[r])];
 #pragma unroll
-            for (int k = 0; k < NR; ++k) reg[k] = lds_at(sw_cur ^ uo[k]);
-          }
-          __syncthreads();
-        };
-        apply_staged(v);
-        if (ADJ) apply_staged(w);
-       }
+              for (int r = 0; r < 4; ++r) {
+                y[r] = cdot2(ldc(T + mat + 4 * r), x[0], ldc(T + mat + 4 * r + 1), x[1]);
+                y[r] = cdot2(C{1, 0}, y[r], ldc(T + mat + 4 * r + 2), x[2]);
+                y[r] = cdot2(C{1, 0}, y[r], ldc(T + mat + 4 * r + 3), x[3]);
+              }
+#pragma unroll
+              for (int r = 0; r < 4; ++r) buf[swz<S>(idx[r])] = y[r];
+            }
+            __syncthreads();
+            if (active) {
+#pragma unroll
+              for (int k = 0; k < NR; ++k) reg[k] = lds_at(sw_cur ^ uo[k]);
+            }
+            __syncthreads();
+          };
+          apply_staged(v);
+          if (ADJ) apply_staged(w);
+        }
       } else if (on && active && type == OP_DIAG && ob) {
         // Entry by entry: one read of the entry, one of its two or four phases (and
         // weights), then each slot times the phase that its own bits, its lane's and the
@@ -860,11 +859,16 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
         // the amplitudes once; complex128 passes, where a second register block would cut the
         // resident waves, multiply the amplitudes entry by entry.
         constexpr bool gather = sizeof(R) == 4;
-        constexpr int NG = gather && ADJ ? NR / 2 : NR;  // slots at a time
+        // Slots at a time: complex64 reverse sweeps walk a run twice, half of the slots each, for the
+        // registers of sweeps that have no such runs but share the kernel.  QAOA on 24 qubits, 32
+        // sets, backward 93.8 ms; all slots at once 96.3, quarters 95.8.  (Four layers of 20 phases
+        // with one parameter, 32 sets on 20 qubits: 4.1 ms, all slots at once 3.7, quarters 5.2.)
+        constexpr int NG = gather && ADJ ? NR / 2 : NR;
         // The reverse sweep's runs are mostly one uncontrolled one-qubit phase each (every run has
         // one parameter): its numbers are read along with its entry, and slot-resident qubits
-        // take one straight line per slot bit instead of a test per slot.  10-qubit ansatz 230 ->
-        // 192 us, 20-qubit ansatz gradients (6 layers, 4 sets, complex64) 1837 -> 1539 us.
+        // take one straight line per slot bit instead of a test per slot.  10-qubit ansatz gradient
+        // 230 -> 195 us, 20-qubit one (6 layers, 4 sets, complex64) 1837 -> 1539 us, 48 uneven
+        // ansatz circuits 2570 -> 2200 us.
         bool done = false;
         if constexpr (ONE) {
           if (count == 1) {
@@ -887,88 +891,88 @@ __device__ __forceinline__ void rb_body(const PassArgs& A, const uint64_t tile, 
             }
           }
         }
-       if (!done) {
+        if (!done) {
 #pragma unroll
-       for (int kg = 0; kg < NR; kg += NG) {
-        uint32_t flips = 0, touched = 0;
-        C ph[gather ? NG : 1];
-        double gws[gather && ADJ ? NG : 1];
+          for (int kg = 0; kg < NR; kg += NG) {
+            uint32_t flips = 0, touched = 0;
+            C ph[gather ? NG : 1];
+            double gws[gather && ADJ ? NG : 1];
 #pragma unroll
-        for (int k = 0; k < (gather ? NG : 0); ++k) {
-          ph[k] = C{1, 0};
-          if (ADJ) gws[k] = 0.0;
-        }
-        for (int e = 0; e < count; ++e) {
-          const PhaseFields f = ld_record(reinterpret_cast<const PhaseFields*>(&A.diag[first + e].ocmask));
-          if ((base & f.ocmask) != f.ocmask) continue;  // an outside control is 0 in this tile
-          const bool in = ((uint32_t)jt & f.tmask) == f.tmask;
-          if (f.where & kWhereSign) {
-            flips ^= in ? f.kmask : 0u;
-            touched |= f.kmask;
-            continue;
-          }
-          const bool two = (f.where & kWhereTwo) != 0, grad = ADJ && f.gtab >= 0;
-          const bool t0 = lane_bit(f.where & 255u), t1 = lane_bit((f.where >> 8) & 255u);
-          for (uint32_t u = 0; u < 4; ++u) {
-            if (((u & 1) && !f.bits0) || ((u & 2) && !f.bits1)) continue;
-            const uint32_t ks = f.kmask & ((u & 1) ? f.bits0 : ~f.bits0) & ((u & 2) ? f.bits1 : ~f.bits1);
-            // half of the table that a lane's second bit selects, then the entry its first does
-            const bool i0 = t0 || (u & 1), i1 = t1 || (u & 2);
-            C p = csel(i0, ldc(T + f.tab + 1), ldc(T + f.tab));
-            if (two) p = csel(i1, csel(i0, ldc(T + f.tab + 3), ldc(T + f.tab + 2)), p);
-            p = csel(in, p, C{1, 0});
-            double gw = 0.0;
-            if (grad) {
-              gw = (double)(i0 ? ldc(T + f.gtab + 1).x : ldc(T + f.gtab).x);
-              if (two) gw = i1 ? (double)(i0 ? ldc(T + f.gtab + 3).x : ldc(T + f.gtab + 2).x) : gw;
+            for (int k = 0; k < (gather ? NG : 0); ++k) {
+              ph[k] = C{1, 0};
+              if (ADJ) gws[k] = 0.0;
             }
-            if constexpr (gather) {
-              const double gs = in ? gw : 0.0;
-#pragma unroll
-              for (int k = 0; k < NG; ++k) {
-                if (!((ks >> (kg + k)) & 1u)) continue;
-                ph[k] = cmul(ph[k], p);
-                if (ADJ) gws[k] += gs;
+            for (int e = 0; e < count; ++e) {
+              const PhaseFields f = ld_record(reinterpret_cast<const PhaseFields*>(&A.diag[first + e].ocmask));
+              if ((base & f.ocmask) != f.ocmask) continue;  // an outside control is 0 in this tile
+              const bool in = ((uint32_t)jt & f.tmask) == f.tmask;
+              if (f.where & kWhereSign) {
+                flips ^= in ? f.kmask : 0u;
+                touched |= f.kmask;
+                continue;
               }
-              continue;
-            }
-            if (grad) {
-              double g = 0.0;
+              const bool two = (f.where & kWhereTwo) != 0, grad = ADJ && f.gtab >= 0;
+              const bool t0 = lane_bit(f.where & 255u), t1 = lane_bit((f.where >> 8) & 255u);
+              for (uint32_t u = 0; u < 4; ++u) {
+                if (((u & 1) && !f.bits0) || ((u & 2) && !f.bits1)) continue;
+                const uint32_t ks = f.kmask & ((u & 1) ? f.bits0 : ~f.bits0) & ((u & 2) ? f.bits1 : ~f.bits1);
+                // half of the table that a lane's second bit selects, then the entry its first does
+                const bool i0 = t0 || (u & 1), i1 = t1 || (u & 2);
+                C p = csel(i0, ldc(T + f.tab + 1), ldc(T + f.tab));
+                if (two) p = csel(i1, csel(i0, ldc(T + f.tab + 3), ldc(T + f.tab + 2)), p);
+                p = csel(in, p, C{1, 0});
+                double gw = 0.0;
+                if (grad) {
+                  gw = (double)(i0 ? ldc(T + f.gtab + 1).x : ldc(T + f.gtab).x);
+                  if (two) gw = i1 ? (double)(i0 ? ldc(T + f.gtab + 3).x : ldc(T + f.gtab + 2).x) : gw;
+                }
+                if constexpr (gather) {
+                  const double gs = in ? gw : 0.0;
 #pragma unroll
-              for (int k = 0; k < NR; ++k)
-                if ((ks >> k) & 1u) g += im_conj_mul(w[k], v[k]);
-              acc = __builtin_fma(in ? gw : 0.0, g, acc);
+                  for (int k = 0; k < NG; ++k) {
+                    if (!((ks >> (kg + k)) & 1u)) continue;
+                    ph[k] = cmul(ph[k], p);
+                    if (ADJ) gws[k] += gs;
+                  }
+                  continue;
+                }
+                if (grad) {
+                  double g = 0.0;
+#pragma unroll
+                  for (int k = 0; k < NR; ++k)
+                    if ((ks >> k) & 1u) g += im_conj_mul(w[k], v[k]);
+                  acc = __builtin_fma(in ? gw : 0.0, g, acc);
+                }
+#pragma unroll
+                for (int k = 0; k < NR; ++k) {
+                  if (!((ks >> k) & 1u)) continue;
+                  if (ADJ) cmul_in(w[k], p);
+                  cmul_in(v[k], p);
+                }
+              }
             }
 #pragma unroll
-            for (int k = 0; k < NR; ++k) {
-              if (!((ks >> k) & 1u)) continue;
-              if (ADJ) cmul_in(w[k], p);
-              cmul_in(v[k], p);
+            for (int i = 0; i < NG; ++i) {
+              const int k = kg + i;
+              const uint32_t f = (flips << (31 - k)) & 0x80000000u;
+              if constexpr (gather) {
+                flip_sign(ph[i], f);
+                if (ADJ) {
+                  double g = gws[i] * im_conj_mul(w[k], v[k]);
+                  cmul_in(w[k], ph[i], g);
+                  cmul_in(v[k], ph[i], g);
+                  acc += g;
+                } else {
+                  cmul_in(v[k], ph[i]);
+                }
+              } else {
+                if (!((touched >> k) & 1u)) continue;
+                flip_sign(v[k], f);
+                if (ADJ) flip_sign(w[k], f);
+              }
             }
           }
         }
-#pragma unroll
-        for (int i = 0; i < NG; ++i) {
-          const int k = kg + i;
-          const uint32_t f = (flips << (31 - k)) & 0x80000000u;
-          if constexpr (gather) {
-            flip_sign(ph[i], f);
-            if (ADJ) {
-              double g = gws[i] * im_conj_mul(w[k], v[k]);
-              cmul_in(w[k], ph[i], g);
-              cmul_in(v[k], ph[i], g);
-              acc += g;
-            } else {
-              cmul_in(v[k], ph[i]);
-            }
-          } else {
-            if (!((touched >> k) & 1u)) continue;
-            flip_sign(v[k], f);
-            if (ADJ) flip_sign(w[k], f);
-          }
-        }
-       }
-       }
       } else if (on && active && type == OP_ZZ) {
         // c(x) = number of edges whose endpoints differ.  Edges come grouped by register
         // class c; an edge of class c differs in slot k iff its thread/outside parity
