@@ -78,7 +78,8 @@ enum FillKind : int32_t {
                       // times the diagonal that its qubit carries from the previous gate of the
                       // chain; count = 1: split into (real matrix, phase) by chain_gate, the
                       // left diagonal carried on, count = 0: the chain's last gate, dense (4
-                      // entries either way)
+                      // entries either way); count = 2: no op, its matrix is multiplied into the
+                      // next gate's (the 4 entries are the identity's)
 };
 struct Fill {
   int32_t kind;
@@ -236,7 +237,7 @@ void block_operands(const cplx* M8, int dtype, double* out);
 // entries and p a unit real or imaginary part (its modulus and R's are carried), so that
 // kernels spend one multiply-add on each of the others; the carried moduli shrink by up to a
 // half per gate.  normalize: R with its moduli, p a phase, and the new carry of modulus 1.
-void chain_gate(const cplx* M, bool normalize, lcplx* carry, cplx* out);
+void chain_gate(const lcplx* M, bool normalize, lcplx* carry, cplx* out);
 // The same for a gate by itself, normalized: M = diag(left[0], left[1]) R diag(1, out[2]).
 void split_gate(const cplx* M, cplx* left, cplx* out);
 // Gates between normalizing ones.  In between, passes store amplitudes up to 2^gates larger per

@@ -141,19 +141,27 @@ void by_itself(std::vector<cplx>& x, const Layers& k, const qsv_gate& g) {
 // General gates one by one: M = diag(l0, l1) [[c, -s], [s, c]] diag(1, p), l carried to the
 // qubit's next gate, its last gate whole; all in double.
 std::vector<cplx> split_in_double(const Layers& k, std::vector<cplx> x) {
-  std::vector<int> left(N, 0);
-  for (const qsv_gate& g : k.gates) left[g.targets[0]] += g.kind == QSV_GATE_U3 || g.kind == QSV_GATE_MAT1;
+  std::vector<int> left(N, 0);  // gates up to the end of the chain: the qubit's next X, or the last
+  std::vector<std::vector<int>> chains(N, std::vector<int>(1, 0));
+  for (const qsv_gate& g : k.gates) {
+    if (g.kind == QSV_GATE_U3 || g.kind == QSV_GATE_MAT1) ++chains[g.targets[0]].back();
+    else if (g.kind == QSV_GATE_X) chains[g.targets[0]].push_back(0);
+  }
+  std::vector<size_t> at(N, 0);
+  for (int q = 0; q < N; ++q) left[q] = chains[q][0];
   std::vector<cplx> carry(2 * N, 1.0);
   for (const qsv_gate& g : k.gates) {
     const int q = g.targets[0];
     if (g.kind != QSV_GATE_U3 && g.kind != QSV_GATE_MAT1) {
       by_itself(x, k, g);
+      if (g.kind == QSV_GATE_X) left[q] = chains[q][++at[q]];
       continue;
     }
     std::vector<cplx> m = numbers(k, g);
     for (int e = 0; e < 4; ++e) m[e] *= carry[2 * q + (e & 1)];
     if (--left[q] == 0) {
       pairs(x, g, [&](cplx& a, cplx& b) { general(m.data(), a, b); });
+      carry[2 * q] = carry[2 * q + 1] = 1.0;
       continue;
     }
     const double a = std::abs(m[0]), b = std::abs(m[2]), nrm = std::hypot(a, b);
@@ -187,7 +195,10 @@ struct Error2 {
 int main(int argc, char** argv) {
   const bool chain = argc > 1 && !strcmp(argv[1], "chain");
   const std::vector<Family> families =
-      chain ? std::vector<Family>{{"U3", {QSV_GATE_U3}}, {"unitaries", {QSV_GATE_MAT1}}}
+      chain ? std::vector<Family>{{"U3", {QSV_GATE_U3}},
+                                  {"unitaries", {QSV_GATE_MAT1}},
+                                  {"U3 twice", {QSV_GATE_U3, QSV_GATE_U3}},
+                                  {"three", {QSV_GATE_MAT1, QSV_GATE_U3, QSV_GATE_MAT1}}}
             : std::vector<Family>{{"RY RZ", {QSV_GATE_RY, QSV_GATE_RZ}},
                                   {"RX RZ", {QSV_GATE_RX, QSV_GATE_RZ}},
                                   {"H T", {QSV_GATE_H, QSV_GATE_T}},
@@ -196,7 +207,7 @@ int main(int argc, char** argv) {
   for (const Family& f : families)
     for (int again = 0; again < 3; ++again)
       for (bool cx : {false, true}) {
-        if (chain && cx) continue;  // (a CX ends its target's chain)
+        if (chain && cx && f.kinds.size() == 1) continue;  // (a CX ends its target's chain)
         Error2 plan, base;
         for (int trial = 0; trial < 10; ++trial) {
           std::mt19937_64 rng(7 + 100 * trial + 10 * again + cx);
