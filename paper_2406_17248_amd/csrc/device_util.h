@@ -118,9 +118,10 @@ __host__ __device__ __forceinline__ uint32_t high_word(float v) {
 // A gate of a phase chain whose matrices keep unit entries (chain_gate): a1 <- a1 p with p = 1 +
 // i t (IMAG: t + i), then (a0, a1) <- (a0 + r0 a1, r1 a0 + a1) (CROSS: (r0 a0 + a1, a0 + r1
 // a1)): one multiply-add per entry that is not 1, 6 instructions per pair, against 12 with a
-// phase and a full real matrix and 16 for the general product.  30-qubit brick in complex128,
-// whole step 210 -> 197 ms (the passes then waited on their waves' latency more than on the
-// vector ALU, see rb_body's SPLIT).
+// phase and a full real matrix and 16 for the general product.  30-qubit brick in complex128, whole
+// step with remaps in two halves (rb_body's SPLIT): 16 instructions 205 ms, 12 172 ms, 6 143 ms;
+// without, where the passes wait on their waves' latency more than on the vector ALU, 16 222 ms, 6
+// 200 ms.
 template <bool IMAG, bool CROSS, typename R, typename C>
 __device__ __forceinline__ void apply2unit(R r0, R r1, R t, C& a0, C& a1) {
   R x = IMAG ? fmaT(t, a1.x, -a1.y) : fmaT(-t, a1.y, a1.x);

@@ -312,7 +312,7 @@ PlanOptions state_plan_options(int32_t dtype, int32_t n, int32_t tile, int32_t a
   // further off than the gates one by one (24 layers on 9 qubits).
   o.split = !adjoint && dtype == QSV_C128;
   // (rb_body's SPLIT: more resident waves pay once there are more workgroups than fit on the
-  // chip at four waves per SIMD: 30 qubits 197 -> 142 ms, a 10-qubit ansatz 231 -> 257 us)
+  // chip at four waves per SIMD: 30 qubits 200 -> 143 ms, a 10-qubit ansatz 231 -> 257 us)
   const int m = std::min<int>(std::max(o.tile_qubits, 2), n);
   o.half_remap = !adjoint && (batch << (n - m)) > kWarmTiles;
   return o;

@@ -13,7 +13,7 @@
 //  pauli_gather  psi[y ^ x] is read from global memory, lambda's partial sums are rounded to
 //                the amplitude type group after group, as the passes per group do.  For states
 //                that caches hold: bound by launches and latency (50 random terms on 11
-//                qubits, 36 launches: 197 -> 30 us), then by the caches (24 qubits,
+//                qubits, 36 launches: 181 -> 31 us), then by the caches (24 qubits,
 //                complex64, H psi 2179 -> 464 us with tiles).
 #include "device_util.h"
 #include "qsv_kernels.h"

@@ -468,8 +468,8 @@ __device__ __forceinline__ uint32_t sign_slots(const DiagEntry* d, int count, ui
 // than it computes (scalar loads, branches, remaps: with four waves per SIMD the vector ALU
 // was busy 56 % of the time), so it wants resident waves: half the exchange buffer and 72
 // registers allow seven per SIMD in complex128 where LDS allowed four (complex64, 16 amplitudes
-// a thread: six).  30-qubit brick in complex128, whole step: 197 -> 142 ms (five waves 164, six
-// 149; eight spill); 27 qubits in complex64: 14.8 -> 13.9 ms.  In launches that leave the chip
+// a thread: six).  30-qubit brick in complex128, whole step: 200 -> 143 ms (five waves 164, six
+// 149; eight spill); 27 qubits in complex64: 14.7 -> 13.7 ms.  In launches that leave the chip
 // idle the two further barriers only cost (10-qubit ansatz 231 -> 257 us); the reverse sweep's
 // registers spill at five waves (24-qubit QAOA gradients 46 -> 54 ms).
 template <typename R> constexpr int kSplitWaves = sizeof(R) == 4 ? 6 : 7;
