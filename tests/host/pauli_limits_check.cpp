@@ -1,6 +1,7 @@
 // Host checks of Pauli-sum plans at their limits (no GPU).  Argument:
-//   plan  planning many groups takes less host time than one pass over the state per group would
-//         at the rate of a large copy.
+//   plan  planning many groups takes less host time than two passes over the state per group
+//         would at the rate of a large copy (0.3 of one pass on the machine that this was written
+//         on; 2.5 when tiles grew over all groups).
 //   grid  launches over batches start no workgroups beyond a batch item's chunks of 256 outputs,
 //         expectations of few chunks in all up to 128 that share them.
 //   order  plans without tiles keep the groups' order.
@@ -40,7 +41,7 @@ static int check_plan() {
     for (char v : seen) bad |= !v;
     printf("weight %d: %zu groups in %zu launches, planned in %.0f ms (a pass each: %.0f ms)\n", weight, groups.size(),
            plan.size(), 1e3 * host, 1e3 * passes);
-    if (!(host <= passes) || plan.size() > groups.size()) bad = 1;
+    if (!(host <= 2.0 * passes) || plan.size() > groups.size()) bad = 1;
   }
   return bad;
 }
